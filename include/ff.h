@@ -42,8 +42,9 @@ typedef enum {
   FF_ERR_HIP = -4            /* a HIP runtime call or kernel launch failed    */
 } ff_status;
 
-/* Operand type of the matrix products; accumulation is always fp32.  In
- * FF_BF16 mode three values are rounded to bfloat16 (round to nearest even)
+/* Operand type of the matrix products; accumulation is always fp32.  FF_F32
+ * operands enter with all 24 bits (as two f16 parts under power-of-two scales;
+ * in ff_pipeline_epoch as they are).  In FF_BF16 mode three values are rounded to bfloat16 (round to nearest even)
  * before they enter a product: R1 the normalised layer input, R2 the weight
  * shadow W_bf16, R3 the gradient rows dZ = 2 dL/dg * h.  Everything else
  * (activities, goodness, loss, master weights, Adam moments) stays fp32. */
@@ -416,7 +417,9 @@ typedef struct {
  *                product stores the gradient for a separate ADAM launch;
  *   ADAM         m = d_out, n = d_in, k = rows of the step;
  *   EMBED_NORM   m rows, n features; aux = the row source mode, plus 16
- *                for bf16 output rows;
+ *                for bf16 output rows, plus 32 when the launch also takes the
+ *                row scales of the layer's fp32 weights (32 alone: a launch
+ *                that only takes row scales, of m rows of up to n features);
  *   LOSS         m rows, n = d_out, k = goodness partials per row; aux bit 0:
  *                the pass also writes the bf16 weight-gradient operand, bit 1:
  *                the next layer's normalised bf16 operand, bit 2: the

@@ -120,7 +120,8 @@ struct StepScratch {
   float *gpart = nullptr; // [col tiles][rows]
   float *g = nullptr;     // [rows]
   float *c = nullptr;     // [rows]
-  float *cs = nullptr;    // [rows] c times the input row scale (raw fp32 input rows)
+  float *q = nullptr;     // [rows] fp32: row factors of the split weight gradient (ffk::DwRows),
+                          // or c times the row scales of raw input rows
   float *lpart = nullptr; // [loss blocks][2]
   float *loss = nullptr;  // [1]
   // Performance-optimised steps (po_classes > 0): the classifier's logit
@@ -137,16 +138,22 @@ struct StepScratch {
   // bf16 FF training steps of an epoch: the weight gradient, stored for an
   // Adam launch of its own (which other streams' products can run beside)
   float *dw = nullptr;      // [d_out][d_in]
+  // fp32 products: the row scales of W, and of input rows that are used in
+  // place; the weight gradient's row exponents
+  float *wscale = nullptr;   // [d_out]
+  float *xscale = nullptr;   // [rows], in the place of xhat
+  int32_t *mpart = nullptr;  // [loss blocks], or [po_row_blocks(rows)]
 };
 
 // train: the scratch of a training step (the bf16 weight-gradient operands);
 // false for forward passes only.  split_adam: a bf16 training step also gets
 // the weight-gradient buffer, and runs its Adam update as a launch of its own;
 // it always does at the sizes where that is faster on one stream
-// (ffk::dw4_split_adam).
+// (ffk::dw4_split_adam).  The fp32 products' scales come last, so that
+// *before_scales (optional) tells the size of everything else.
 void carve_step(Carver &cv, StepScratch &s, int rows, int d_in, int d_out, int dtype, bool need_h,
                 bool need_g, bool need_loss, int po_classes = 0, bool train = true,
-                bool split_adam = false) {
+                bool split_adam = false, size_t *before_scales = nullptr) {
   if (po_classes > 0) {
     s.G = static_cast<float *>(cv.take((size_t)rows * po_classes * 4));
     s.lrow = static_cast<float *>(cv.take((size_t)rows * 4));
@@ -159,7 +166,7 @@ void carve_step(Carver &cv, StepScratch &s, int rows, int d_in, int d_out, int d
   s.gpart = static_cast<float *>(cv.take((size_t)ffk::fwd_col_tiles_max(d_out) * rows * 4));
   if (need_g) s.g = static_cast<float *>(cv.take((size_t)rows * 4));
   s.c = static_cast<float *>(cv.take((size_t)rows * 4));
-  s.cs = static_cast<float *>(cv.take((size_t)rows * 4));
+  s.q = static_cast<float *>(cv.take((size_t)rows * 4));
   s.lpart = static_cast<float *>(cv.take((size_t)ffk::loss_blocks(rows) * 2 * 4));
   if (need_loss) s.loss = static_cast<float *>(cv.take(4));
   if (train && dtype == FF_BF16 && po_classes == 0 && d_in > 0) {
@@ -169,6 +176,14 @@ void carve_step(Carver &cv, StepScratch &s, int rows, int d_in, int d_out, int d
     s.dbp = static_cast<float *>(cv.take((size_t)ffk::loss_blocks(rows) * d_out * 4));
     if (split_adam || ffk::dw4_split_adam(d_out, d_in))
       s.dw = static_cast<float *>(cv.take((size_t)d_out * d_in * 4));
+  }
+  if (before_scales) *before_scales = cv.off;
+  if (dtype == FF_F32) {
+    s.xscale = static_cast<float *>(s.xhat);  // one or the other is used
+    s.wscale = static_cast<float *>(cv.take((size_t)d_out * 4));
+    if (train)
+      s.mpart = static_cast<int32_t *>(
+          cv.take((size_t)(po_classes > 0 ? ffk::po_row_blocks(rows) : ffk::loss_blocks(rows)) * 4));
   }
 }
 
@@ -228,49 +243,87 @@ inline const void *weight_operand(const ff_layer *L, int dtype) {
   return dtype == FF_BF16 ? static_cast<const void *>(L->W_bf16) : static_cast<const void *>(L->W);
 }
 
+// The row scales of a layer's weights, into `scale` [d_out].
+ffk::RowScaleJob weight_scales(const ff_layer *L, float *scale) {
+  return ffk::RowScaleJob{L->W, scale, L->d_out, L->d_in};
+}
+
+// Row scales of `count` matrices, kMaxScaleJobs per launch.
+hipError_t row_scales(const ffk::RowScaleJob *jobs, int count, hipStream_t st) {
+  for (int j = 0; j < count; j += ffk::kMaxScaleJobs) {
+    const int n = std::min(count - j, ffk::kMaxScaleJobs);
+    double bytes = 0;
+    int rows = 0, d = 0;
+    for (int i = j; i < j + n; ++i) {
+      bytes += (double)jobs[i].n * (jobs[i].d + 1) * 4.0;
+      rows += jobs[i].n;
+      d = std::max(d, jobs[i].d);
+    }
+    const hipError_t e = launch(FF_KERNEL_EMBED_NORM, Sizes{rows, d, 0, 32}, 0.0, bytes, st,
+                                [&] { return ffk::launch_row_scales(jobs + j, n, st); });
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Normalised operand rows for a layer: fp32 rows may be used in place when
 // already normalised; otherwise (and always for bf16) the embed/normalise
 // kernel writes them into scratch.
 hipError_t embed_norm(const ffk::RowMap &src, int rows, int d, float eps, bool normalise,
-                      bool bf16, void *out, hipStream_t st, float *scale_out = nullptr) {
+                      bool bf16, void *out, hipStream_t st, float *scale_out = nullptr,
+                      const ffk::RowScaleJob *scales = nullptr) {
   // unique source rows: a chunk's positives and negatives share base rows, and
   // label expansion reads each base row once per label
   const double src_rows = src.mode == ffk::PAIRS    ? (double)src.n_pos
                           : src.mode == ffk::EXPAND ? (double)rows / src.n_classes
                                                     : (double)rows;
   const double bytes = src_rows * d * 4.0 + (double)rows * d * (bf16 ? 2 : 4) +
-                       (scale_out ? rows * 4.0 : 0.0);
-  return launch(FF_KERNEL_EMBED_NORM, Sizes{rows, d, 0, src.mode | (bf16 ? 16 : 0)}, 0.0,
-                bytes, st, [&] {
-    return ffk::launch_embed_norm(src, rows, d, eps, normalise, bf16, out, scale_out, st);
+                       (scale_out ? rows * 4.0 : 0.0) +
+                       (scales ? (double)scales->n * (scales->d + 1) * 4.0 : 0.0);
+  return launch(FF_KERNEL_EMBED_NORM,
+                Sizes{rows, d, 0, src.mode | (bf16 ? 16 : 0) | (scales ? 32 : 0)}, 0.0, bytes, st,
+                [&] {
+    return ffk::launch_embed_norm(src, rows, d, eps, normalise, bf16, out, scale_out, st, scales);
   });
 }
 
-hipError_t fwd(int dtype, const void *X, const void *W, const float *bias, const float *rowscale,
+// Row factors and scales of a forward product's operands (fp32; null for bf16).
+struct FwdScales {
+  const float *row = nullptr;  // [M] normalisation of raw input rows
+  const float *x = nullptr;    // [M] row scales of input rows used in place
+  const float *w = nullptr;    // [N] row scales of W; null: fp32 matrix instructions
+};
+
+hipError_t fwd(int dtype, const void *X, const void *W, const float *bias, const FwdScales &fs,
                int M, int N, int K, float *H, float *gpart, hipStream_t st) {
   const double eb = (double)elem_bytes(dtype);
-  const double nt = ffk::fwd_col_tiles(M, N, dtype);
+  const double nt = ffk::fwd_col_tiles(M, N, dtype, fs.w != nullptr);
   const double bytes = (double)M * K * eb + (double)N * K * eb + N * 4.0 +
-                       (rowscale ? M * 4.0 : 0.0) + (H ? (double)M * N * 4.0 : 0.0) +
-                       nt * M * 4.0;
+                       (fs.row || fs.x ? M * 4.0 : 0.0) + (fs.w ? N * 4.0 : 0.0) +
+                       (H ? (double)M * N * 4.0 : 0.0) + nt * M * 4.0;
   return launch(FF_KERNEL_FORWARD, Sizes{M, N, K, 0}, gemm_flops(M, N, K), bytes, st, [&] {
-    return ffk::launch_fwd(dtype, X, W, bias, rowscale, M, N, K, H, gpart, st);
+    if (dtype == FF_BF16)
+      return ffk::launch_fwd_bf16(static_cast<const uint16_t *>(X),
+                                  static_cast<const uint16_t *>(W), bias, M, N, K, H, gpart, st);
+    return ffk::launch_fwd_f32(static_cast<const float *>(X), static_cast<const float *>(W), bias,
+                               fs.row, fs.x, fs.w, M, N, K, H, gpart, st);
   });
 }
 
 // Shared-base layer-0 forward over M base rows expanded by ex (bytes: the
 // base rows, W, the expanded H and partials).
 hipError_t fwd_expand(int dtype, const void *X, const void *W, const float *bias,
-                      const ffk::LabelExpand &ex, int M, int N, int K, float *H, float *gpart,
-                      hipStream_t st) {
+                      const ffk::LabelExpand &ex, const float *wscale, int M, int N, int K,
+                      float *H, float *gpart, hipStream_t st) {
   const double eb = (double)elem_bytes(dtype);
   const double rows_out = (double)M * ex.n_classes;
   const double nt = ffk::fwd_expand_col_tiles(M, N, dtype);
   const double bytes = (double)M * K * eb + (double)N * K * eb + N * 4.0 + M * 4.0 +
-                       (H ? rows_out * N * 4.0 : 0.0) + nt * rows_out * 4.0;
+                       (wscale ? N * 4.0 : 0.0) + (H ? rows_out * N * 4.0 : 0.0) +
+                       nt * rows_out * 4.0;
   return launch(FF_KERNEL_FORWARD, Sizes{M, N, K, ex.n_classes}, gemm_flops(M, N, K), bytes, st,
                 [&] {
-    return ffk::launch_fwd_expand(dtype, X, W, bias, ex, M, N, K, H, gpart, st);
+    return ffk::launch_fwd_expand(dtype, X, W, bias, ex, wscale, M, N, K, H, gpart, st);
   });
 }
 
@@ -281,21 +334,6 @@ hipError_t goodness_sum(const float *gpart, int nt, int R, float *g, float *out,
   return launch(FF_KERNEL_GOODNESS, Sizes{R, nt, 0, 0}, 0.0, bytes, st, [&] {
     return ffk::launch_goodness(gpart, nt, R, g, out, accumulate, s_out, norm_eps, st);
   });
-}
-
-// Normalised operand rows for a layer: fp32 rows may be used in place when
-// already normalised; otherwise (and always for bf16) the embed/normalise
-// kernel writes them into scratch.
-ff_status stage_input(const ffk::RowMap &src, int rows, int d_in, bool normalised, int dtype,
-                      float norm_eps, void *scratch, const void **operand, hipStream_t st) {
-  const bool bf16 = dtype == FF_BF16;
-  if (normalised && !bf16 && src.mode == ffk::ROWS) {
-    *operand = src.base;
-    return FF_OK;
-  }
-  FF_HIP(embed_norm(src, rows, d_in, norm_eps, !normalised, bf16, scratch, st));
-  *operand = scratch;
-  return FF_OK;
 }
 
 // Input rows of a layer.  `rowscale` (fp32 only) marks raw hidden-activity rows
@@ -329,20 +367,56 @@ LayerInput raw_rows(const float *x, const float *rowscale) {
   return in;
 }
 
+// Operand rows of a layer's products and their scales, with the scales of the
+// layer's weights (fp32): raw rows with their rowscale as they are; fp32 rows
+// that are already normalised in place, with row scales of their own (their
+// size is the caller's); anything else through the embed/normalise kernel into
+// scratch.  One launch in every case but bf16 rows handed over by the previous
+// layer (in.xt), which need none.  split = false: no scales, for products on
+// the fp32 matrix instructions.
+ff_status stage_input(const ff_layer *L, const ff_hparams *hp, const LayerInput &in, int rows,
+                      StepScratch &s, bool split, const void **operand, FwdScales *fs,
+                      hipStream_t st) {
+  const bool bf16 = hp->dtype == FF_BF16;
+  *operand = in.src.base;
+  *fs = FwdScales();
+  if (in.xt) return FF_OK;
+  if (bf16) {
+    *operand = s.xhat;
+    FF_HIP(embed_norm(in.src, rows, L->d_in, hp->norm_eps, !in.normalised, true, s.xhat, st));
+    return FF_OK;
+  }
+  if (split) fs->w = s.wscale;
+  const ffk::RowScaleJob wj = weight_scales(L, s.wscale);
+  if (in.rowscale) {
+    fs->row = in.rowscale;
+    if (split) FF_HIP(row_scales(&wj, 1, st));
+  } else if (in.normalised && in.src.mode == ffk::ROWS) {
+    if (!split) return FF_OK;
+    const ffk::RowScaleJob jobs[2] = {{in.src.base, s.xscale, rows, L->d_in}, wj};
+    fs->x = s.xscale;
+    FF_HIP(row_scales(jobs, 2, st));
+  } else {
+    *operand = s.xhat;
+    FF_HIP(embed_norm(in.src, rows, L->d_in, hp->norm_eps, !in.normalised, false, s.xhat, st,
+                      nullptr, split ? &wj : nullptr));
+  }
+  return FF_OK;
+}
+
 // Forward of one layer; `s_next` (optional) receives the output rows'
 // normalisation for the next layer.
 ff_status forward_core(const ff_layer *L, const ff_hparams *hp, const LayerInput &in, int rows,
                        float *h_out, float *goodness, float *s_next, StepScratch &s,
-                       hipStream_t st) {
-  const void *xop = in.src.base;
-  if (!in.rowscale)
-    FF_TRY(stage_input(in.src, rows, L->d_in, in.normalised, hp->dtype, hp->norm_eps, s.xhat,
-                       &xop, st));
-  FF_HIP(fwd(hp->dtype, xop, weight_operand(L, hp->dtype), L->b, in.rowscale, rows, L->d_out,
-             L->d_in, h_out, s.gpart, st));
+                       hipStream_t st, bool split = true) {
+  const void *xop = nullptr;
+  FwdScales fs;
+  FF_TRY(stage_input(L, hp, in, rows, s, split, &xop, &fs, st));
+  FF_HIP(fwd(hp->dtype, xop, weight_operand(L, hp->dtype), L->b, fs, rows, L->d_out, L->d_in,
+             h_out, s.gpart, st));
   if (goodness || s_next)
-    FF_HIP(goodness_sum(s.gpart, ffk::fwd_col_tiles(rows, L->d_out, hp->dtype), rows, goodness,
-                        nullptr, 0, s_next, hp->norm_eps, st));
+    FF_HIP(goodness_sum(s.gpart, ffk::fwd_col_tiles(rows, L->d_out, hp->dtype, split), rows,
+                        goodness, nullptr, 0, s_next, hp->norm_eps, st));
   return FF_OK;
 }
 
@@ -358,27 +432,47 @@ ffk::AdamArgs adam_args(const ff_hparams *hp, int64_t t) {
   return a;
 }
 
+// fp32 weight gradient and Adam update of a layer from its rows H (dZ = c H)
+// and input rows X.  split = false: on the fp32 matrix instructions, rows.q
+// holding c s (when there is an s).
+ff_status dw_adam_f32(ff_layer *L, const float *H, const float *X, const ffk::DwRows &rows,
+                      bool split, int R, const ffk::AdamArgs &a, const ffk::LossFinish &lf,
+                      hipStream_t st) {
+  const double params = (double)L->d_out * L->d_in;
+  const double bytes = (double)R * (L->d_out + L->d_in) * 4.0 + R * (rows.s ? 12.0 : 8.0) +
+                       params * 24.0 + L->d_out * 24.0;
+  FF_HIP(launch(FF_KERNEL_DW_ADAM, Sizes{L->d_out, L->d_in, R, 0},
+                gemm_flops(L->d_out, L->d_in, R), bytes, st, [&] {
+    if (split)
+      return ffk::launch_dw_adam_split(H, X, rows, L->d_out, L->d_in, R, L->W, L->mW, L->vW, L->b,
+                                       L->mb, L->vb, a, lf, st);
+    return ffk::launch_dw_adam_f32(H, rows.c, X, rows.s ? rows.q : nullptr, L->d_out, L->d_in, R,
+                                   L->W, L->mW, L->vW, L->b, L->mb, L->vb, a, lf, st);
+  }));
+  return FF_OK;
+}
+
 // One training step (n_pos positives first); `s_next` as in forward_core.
 // out_ready (optional) is recorded on st once the step's outputs for the next
 // layer (h_out, s_next or nx) are written, before the weight update.
+// split = false: fp32 products on the fp32 matrix instructions.
 ff_status step_core(ff_layer *L, const ff_hparams *hp, const LayerInput &in, int n_pos,
                     int n_neg, float *h_out, float *goodness, float *loss, float *s_next,
                     StepScratch &s, hipStream_t st, const NextBf16 *nx = nullptr,
-                    hipEvent_t out_ready = nullptr) {
+                    hipEvent_t out_ready = nullptr, bool split = true) {
   const int R = n_pos + n_neg;
-  const void *xop = in.src.base;
   if ((in.xt || nx) && !(hp->dtype == FF_BF16 && s.dzt && !in.rowscale))
     return fail(FF_ERR_INVALID_ARG, "bf16 operand handoff outside a bf16 training step");
-  if (!in.rowscale && !in.xt)
-    FF_TRY(stage_input(in.src, R, L->d_in, in.normalised, hp->dtype, hp->norm_eps, s.xhat, &xop,
-                       st));
+  const void *xop = nullptr;
+  FwdScales fs;
+  FF_TRY(stage_input(L, hp, in, R, s, split, &xop, &fs, st));
   float *H = h_out ? h_out : s.h;
   float *g = goodness ? goodness : s.g;
   float *lo = loss ? loss : s.loss;
-  const int nt = ffk::fwd_col_tiles(R, L->d_out, hp->dtype);
-  FF_HIP(fwd(hp->dtype, xop, weight_operand(L, hp->dtype), L->b, in.rowscale, R, L->d_out,
-             L->d_in, H, s.gpart, st));
-  if (hp->dtype == FF_BF16 && s.dzt) {
+  const int nt = ffk::fwd_col_tiles(R, L->d_out, hp->dtype, split);
+  FF_HIP(fwd(hp->dtype, xop, weight_operand(L, hp->dtype), L->b, fs, R, L->d_out, L->d_in, H,
+             s.gpart, st));
+  if (hp->dtype == FF_BF16) {
     // bf16: the weight gradient as an NT product over the rows.  The loss pass
     // also writes bf16(c . H)^T and the db partials; x_hat^T is transposed from
     // the normalised bf16 rows.
@@ -429,37 +523,28 @@ ff_status step_core(ff_layer *L, const ff_hparams *hp, const LayerInput &in, int
     L->step = t;
     return FF_OK;
   }
-  float *cs = in.rowscale ? s.cs : nullptr;
+  const int nrb = ffk::loss_blocks(R);
   FF_HIP(launch(FF_KERNEL_LOSS, Sizes{R, L->d_out, nt, 0}, 0.0,
                 (double)nt * R * 4.0 + R * (g ? 8.0 : 4.0) + (s_next ? R * 4.0 : 0.0) +
-                    (cs ? R * 8.0 : 0.0),
+                    (split ? R * (fs.x ? 8.0 : 4.0) : (in.rowscale ? R * 8.0 : 0.0)),
                 st, [&] {
                   return ffk::launch_loss(s.gpart, nt, R, n_pos, hp->theta, g, s.c, s.lpart,
-                                          s_next, hp->norm_eps, in.rowscale, cs, st);
+                                          s_next, hp->norm_eps, split ? nullptr : in.rowscale,
+                                          !split && in.rowscale ? s.q : nullptr, fs.x,
+                                          split ? s.q : nullptr, split ? s.mpart : nullptr, st);
                 }));
   if (out_ready) FF_HIP(hipEventRecord(out_ready, st));
   ffk::LossFinish lf;
   lf.lpart = s.lpart;
-  lf.nblk = ffk::loss_blocks(R);
+  lf.nblk = nrb;
   lf.n_pos = n_pos;
   lf.n_neg = n_neg;
   lf.loss = lo;
   // the update is t = step + 1; the count moves only once its launch is enqueued
   const int64_t t = L->step + 1;
-  const ffk::AdamArgs a = adam_args(hp, t);
-  {
-    const double eb = (double)elem_bytes(hp->dtype);
-    const double params = (double)L->d_out * L->d_in;
-    const double bytes = (double)R * L->d_out * 4.0 + (double)R * L->d_in * eb +
-                         R * (in.rowscale ? 8.0 : 4.0) +
-                         params * (24.0 + (hp->dtype == FF_BF16 ? 2.0 : 0.0)) + L->d_out * 24.0;
-    FF_HIP(launch(FF_KERNEL_DW_ADAM, Sizes{L->d_out, L->d_in, R, 0},
-                  gemm_flops(L->d_out, L->d_in, R), bytes, st, [&] {
-      return ffk::launch_dw_adam(hp->dtype, H, s.c, xop, cs, L->d_out, L->d_in, R, L->W,
-                                 L->mW, L->vW, hp->dtype == FF_BF16 ? L->W_bf16 : nullptr, L->b,
-                                 L->mb, L->vb, a, lf, st);
-    }));
-  }
+  FF_TRY(dw_adam_f32(L, H, static_cast<const float *>(xop),
+                     ffk::DwRows{s.c, s.q, in.rowscale, s.mpart, nrb}, split, R, adam_args(hp, t),
+                     lf, st));
   L->step = t;
   return FF_OK;
 }
@@ -473,15 +558,15 @@ ff_status po_step_core(ff_layer *L, ff_head *head, const ff_hparams *hp, const f
                        float *loss, float *s_next, StepScratch &s, hipStream_t st,
                        hipEvent_t out_ready = nullptr) {
   const int C = head->n_classes, D = L->d_out;
-  const void *xop = in.src.base;
-  if (!in.rowscale)
-    FF_TRY(stage_input(in.src, R, L->d_in, in.normalised, hp->dtype, hp->norm_eps, s.xhat, &xop,
-                       st));
+  const bool bf16 = hp->dtype == FF_BF16;
+  const void *xop = nullptr;
+  FwdScales fs;
+  FF_TRY(stage_input(L, hp, in, R, s, true, &xop, &fs, st));
   float *H = h_out ? h_out : s.h;
-  FF_HIP(fwd(hp->dtype, xop, weight_operand(L, hp->dtype), L->b, in.rowscale, R, D, L->d_in, H,
-             s.gpart, st));
+  FF_HIP(fwd(hp->dtype, xop, weight_operand(L, hp->dtype), L->b, fs, R, D, L->d_in, H, s.gpart,
+             st));
   if (s_next)
-    FF_HIP(goodness_sum(s.gpart, ffk::fwd_col_tiles(R, D, hp->dtype), R, nullptr, nullptr, 0,
+    FF_HIP(goodness_sum(s.gpart, ffk::fwd_col_tiles(R, D, hp->dtype, true), R, nullptr, nullptr, 0,
                         s_next, hp->norm_eps, st));
   if (out_ready) FF_HIP(hipEventRecord(out_ready, st));
   ffk::HeadFeatures f{};
@@ -502,7 +587,9 @@ ff_status po_step_core(ff_layer *L, ff_head *head, const ff_hparams *hp, const f
                 }));
   FF_HIP(launch(FF_KERNEL_HEAD, Sizes{R, C, D, 2}, 2.0 * R * C * D,
                 2.0 * hbytes + (double)C * D * 4.0, st, [&] {
-    return ffk::launch_po_dz(H, s.G, head->W, R, D, C, s.dz, s.c, st);
+    return bf16 ? ffk::launch_po_dz(H, s.G, head->W, R, D, C, s.dz, s.c, st)
+                : ffk::launch_po_dz_rows(H, s.G, head->W, R, D, C, s.dz, s.c, fs.x, s.q, s.mpart,
+                                         st);
   }));
   FF_HIP(launch(FF_KERNEL_HEAD, Sizes{R, C, D, 3}, 2.0 * R * C * D,
                 hbytes + (double)splits * C * D * 4.0, st, [&] {
@@ -516,22 +603,39 @@ ff_status po_step_core(ff_layer *L, ff_head *head, const ff_hparams *hp, const f
                                                ah, loss ? loss : s.loss, st);
                 }));
   ++head->step;
-  // dW = dZ^T x_hat, db = sum dZ: the weight-gradient product with row scale
-  // c = 1, so with raw input rows the product's factor c * s is the input row
-  // scale s itself
+  // dW = dZ^T x_hat, db = sum dZ: the weight-gradient product with c = 1
   const ffk::AdamArgs a = adam_args(hp, L->step + 1);
   ffk::LossFinish lf{};
-  const double eb = (double)elem_bytes(hp->dtype);
-  const double params = (double)D * L->d_in;
-  const double bytes = hbytes + (double)R * L->d_in * eb + R * (in.rowscale ? 8.0 : 4.0) +
-                       params * (24.0 + (hp->dtype == FF_BF16 ? 2.0 : 0.0)) + D * 24.0;
-  FF_HIP(launch(FF_KERNEL_DW_ADAM, Sizes{D, L->d_in, R, 0}, gemm_flops(D, L->d_in, R), bytes,
-                st, [&] {
-    return ffk::launch_dw_adam(hp->dtype, s.dz, s.c, xop, in.rowscale, D, L->d_in, R, L->W,
-                               L->mW, L->vW, hp->dtype == FF_BF16 ? L->W_bf16 : nullptr, L->b,
-                               L->mb, L->vb, a, lf, st);
-  }));
+  if (bf16) {
+    const double params = (double)D * L->d_in;
+    const double bytes = hbytes + (double)R * L->d_in * 2.0 + R * 4.0 + params * 26.0 + D * 24.0;
+    FF_HIP(launch(FF_KERNEL_DW_ADAM, Sizes{D, L->d_in, R, 0}, gemm_flops(D, L->d_in, R), bytes,
+                  st, [&] {
+      return ffk::launch_dw_adam_bf16(s.dz, s.c, static_cast<const uint16_t *>(xop), D, L->d_in,
+                                      R, L->W, L->mW, L->vW, L->W_bf16, L->b, L->mb, L->vb, a, lf,
+                                      st);
+    }));
+  } else {
+    FF_TRY(dw_adam_f32(L, s.dz, static_cast<const float *>(xop),
+                       ffk::DwRows{s.c, s.q, in.rowscale, s.mpart, ffk::po_row_blocks(R)}, true,
+                       R, a, lf, st));
+  }
   ++L->step;
+  return FF_OK;
+}
+
+// The row scales of every layer's weights, one after another in `scales`
+// [sum of d_out]; at[l]: layer l's.
+ff_status stack_scales(const ff_layer *layers, int n_layers, float *scales,
+                       std::vector<const float *> &at, hipStream_t st) {
+  std::vector<ffk::RowScaleJob> jobs;
+  at.clear();
+  for (int l = 0; l < n_layers; ++l) {
+    jobs.push_back(weight_scales(&layers[l], scales));
+    at.push_back(scales);
+    scales += layers[l].d_out;
+  }
+  FF_HIP(row_scales(jobs.data(), n_layers, st));
   return FF_OK;
 }
 
@@ -641,7 +745,10 @@ ff_status ff_layer_step(ff_layer *L, const ff_hparams *hp, const float *x, int32
 // GPU holds its own copy).  In host code `scratch` only names the symbol; its
 // device address, per device, comes from hipGetSymbolAddress.
 // ---------------------------------------------------------------------------
-static __device__ __align__(256) unsigned char scratch[FF_NOALLOC_SCRATCH_BYTES];
+// The fp32 products' scales (at most FF_MAX_WIDTH weight rows and one exponent
+// per 64 batch rows) have room of their own past the documented size.
+constexpr size_t kNoallocScales = 8u << 20;
+static __device__ __align__(256) unsigned char scratch[FF_NOALLOC_SCRATCH_BYTES + kNoallocScales];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -684,9 +791,10 @@ ff_status ff_layer_step_noalloc(ff_layer *L, const ff_hparams *hp, const float *
   // h_out is NULL, the goodness and loss only when not passed
   Carver size_cv(nullptr);
   StepScratch tmp;
-  carve_step(size_cv, tmp, R, L->d_in, L->d_out, hp->dtype, !h_out, !goodness, !loss);
-  const size_t need = size_cv.off;
-  if (need > (size_t)FF_NOALLOC_SCRATCH_BYTES)
+  size_t need = 0;
+  carve_step(size_cv, tmp, R, L->d_in, L->d_out, hp->dtype, !h_out, !goodness, !loss, 0, true,
+             false, &need);
+  if (need > (size_t)FF_NOALLOC_SCRATCH_BYTES || size_cv.off - need > kNoallocScales)
     return fail(FF_ERR_UNSUPPORTED,
                 "%d rows of %d -> %d need %zu bytes of scratch; the no-allocation step holds %zu "
                 "(pass h_out, or use ff_layer_step with a workspace)",
@@ -728,6 +836,7 @@ struct ScoreScratch {
   float *ls = nullptr;            // [images] shared-base scale
   float *h[2] = {nullptr, nullptr};  // [rows][max d_out]; h[1] for fp32 stacks of 3+ layers
   float *rs = nullptr;            // [rows] fp32
+  float *wscale = nullptr;        // fp32: [sum of d_out] row scales of every layer's W
   float *gpart = nullptr;         // [max col tiles][rows]
   float *scores = nullptr;        // [n][C] when the caller passes none
 };
@@ -737,7 +846,9 @@ void carve_score(Carver &cv, ScoreScratch &s, const ff_layer *layers, int n_laye
   const int nb = std::min(n, kScoreBlockImages);
   const size_t rows = (size_t)nb * C;
   int max_in = 0, max_out = 0, max_nt = 0;
+  size_t total_out = 0;
   for (int l = 0; l < n_layers; ++l) {
+    total_out += layers[l].d_out;
     max_in = std::max(max_in, layers[l].d_in);
     max_out = std::max(max_out, layers[l].d_out);
     max_nt = std::max(max_nt, ffk::fwd_col_tiles_max(layers[l].d_out));
@@ -752,6 +863,7 @@ void carve_score(Carver &cv, ScoreScratch &s, const ff_layer *layers, int n_laye
   if (n_layers > 1 && !bf16) s.rs = static_cast<float *>(cv.take(rows * 4));
   s.gpart = static_cast<float *>(cv.take((size_t)max_nt * rows * 4));
   if (need_scores) s.scores = static_cast<float *>(cv.take((size_t)n * C * 4));
+  if (!bf16) s.wscale = static_cast<float *>(cv.take((size_t)total_out * 4));
 }
 }  // namespace
 
@@ -786,6 +898,8 @@ ff_status score_run(const ff_layer *layers, int32_t n_layers, int32_t first_scor
                     const int32_t *exclude, float *S, int32_t *pred, ScoreScratch &s,
                     hipStream_t st) {
   const bool bf16 = hp->dtype == FF_BF16;
+  std::vector<const float *> wscale;
+  if (!bf16) FF_TRY(stack_scales(layers, n_layers, s.wscale, wscale, st));
   for (int n0 = 0; n0 < n; n0 += kScoreBlockImages) {
     const int nb = std::min(kScoreBlockImages, n - n0);
     const int rows = nb * n_classes;
@@ -803,17 +917,20 @@ ff_status score_run(const ff_layer *layers, int32_t n_layers, int32_t first_scor
       const bool raw = l > 0 && !bf16;
       const void *X = raw ? s.h[(l - 1) & 1] : s.x;
       float *H = last ? nullptr : s.h[bf16 ? 0 : (l & 1)];
-      int nt = ffk::fwd_col_tiles(rows, L->d_out, hp->dtype);
+      int nt = ffk::fwd_col_tiles(rows, L->d_out, hp->dtype, true);
       if (l == 0 && shared) {
         ffk::LabelExpand ex{};
         ex.n_classes = n_classes;
         ex.scale = s.ls;
-        FF_HIP(fwd_expand(hp->dtype, X, weight_operand(L, hp->dtype), L->b, ex, nb, L->d_out,
-                          L->d_in, H, s.gpart, st));
+        FF_HIP(fwd_expand(hp->dtype, X, weight_operand(L, hp->dtype), L->b, ex,
+                          bf16 ? nullptr : wscale[l], nb, L->d_out, L->d_in, H, s.gpart, st));
         nt = ffk::fwd_expand_col_tiles(nb, L->d_out, hp->dtype);
       } else {
-        FF_HIP(fwd(hp->dtype, X, weight_operand(L, hp->dtype), L->b, raw ? s.rs : nullptr, rows,
-                   L->d_out, L->d_in, H, s.gpart, st));
+        FwdScales fs;
+        fs.row = raw ? s.rs : nullptr;
+        fs.w = bf16 ? nullptr : wscale[l];
+        FF_HIP(fwd(hp->dtype, X, weight_operand(L, hp->dtype), L->b, fs, rows, L->d_out, L->d_in,
+                   H, s.gpart, st));
       }
       const bool scored = l >= first_scored_layer;
       float *s_next = !last && !bf16 ? s.rs : nullptr;
@@ -884,6 +1001,7 @@ struct HeadScratch {
   float *lrow = nullptr;        // [n]
   float *part = nullptr;        // [splits][C][d_feat]
   float *loss = nullptr;        // [1]
+  float *wscale = nullptr;      // fp32: [sum of d_out] row scales of every layer's W
 };
 
 int head_feat_width(const ff_layer *layers, int n_layers, int first) {
@@ -914,6 +1032,7 @@ void carve_head(Carver &cv, HeadScratch &hs, const ff_layer *layers, int L, int 
   hs.part = static_cast<float *>(cv.take((size_t)ffk::head_grad_splits(n) * C *
                                          head_feat_width(layers, L, first) * 4));
   hs.loss = static_cast<float *>(cv.take(4));
+  if (!bf16) hs.wscale = static_cast<float *>(cv.take((size_t)head_feat_width(layers, L, 0) * 4));
 }
 
 ff_status check_head(const ff_layer *layers, int n_layers, int first, const ff_hparams *hp,
@@ -948,21 +1067,24 @@ ff_status head_features(const ff_layer *layers, int L, int first, const ff_hpara
   m.base = x_base;
   m.mode = ffk::NEUTRAL;
   m.n_classes = C;
+  std::vector<const float *> wscale;
+  if (!bf16) FF_TRY(stack_scales(layers, L, hs.wscale, wscale, st));
   FF_HIP(embed_norm(m, n, layers[0].d_in, hp->norm_eps, true, bf16, hs.x0, st));
   for (int l = 0; l < L; ++l) {
     const ff_layer *Ly = &layers[l];
     const void *X = hs.x0;
-    const float *rs = nullptr;
+    FwdScales fs;
+    if (!bf16) fs.w = wscale[l];
     if (l > 0 && bf16) {
       FF_HIP(embed_norm(rows_of(hs.h[l - 1]), n, Ly->d_in, hp->norm_eps, true, true, hs.xb, st));
       X = hs.xb;
     } else if (l > 0) {
       X = hs.h[l - 1];
-      rs = hs.s[l - 1];
+      fs.row = hs.s[l - 1];
     }
-    FF_HIP(fwd(hp->dtype, X, weight_operand(Ly, hp->dtype), Ly->b, rs, n, Ly->d_out, Ly->d_in,
+    FF_HIP(fwd(hp->dtype, X, weight_operand(Ly, hp->dtype), Ly->b, fs, n, Ly->d_out, Ly->d_in,
                hs.h[l], hs.gpart, st));
-    FF_HIP(goodness_sum(hs.gpart, ffk::fwd_col_tiles(n, Ly->d_out, hp->dtype), n, nullptr,
+    FF_HIP(goodness_sum(hs.gpart, ffk::fwd_col_tiles(n, Ly->d_out, hp->dtype, true), n, nullptr,
                         nullptr, 0, hs.s[l], hp->norm_eps, st));
   }
   f = ffk::HeadFeatures{};
@@ -1096,6 +1218,13 @@ struct PipeScratch {
 // StepScratch::dw), by schedule.
 constexpr bool kSplitAdamPipelined = true;
 constexpr bool kSplitAdamSequential = false;
+// Whether the fp32 products of ff_pipeline_epoch run as split products.  They do
+// not: the steps of an epoch amplify any change of rounding (after two epochs of
+// nine chunks, 784 -> 2000 x 4, the split's results, though each product is closer
+// to 64 bits, were up to 6e-2 from those of the fp32 instructions in the last
+// layers' moments, past the 2e-3 that callers compare epochs at), so an epoch
+// keeps the arithmetic that it has had.
+constexpr bool kSplitEpoch = false;
 // Whether pipelined bf16 FF epochs hand the next layer its operand from the
 // loss pass (PipeScratch::bf16_handoff) instead of the activities.
 constexpr bool kBf16Handoff = true;
@@ -1179,7 +1308,7 @@ namespace {
 template <class Input0, class Step>
 ff_status epoch_core(ff_layer *layers, int n_layers, const ff_hparams *hp, int n, int chunk_pairs,
                      int epochs, int schedule, void *const *streams, float *loss_trace,
-                     PipeScratch &p, int rpp, Input0 input0, Step step) {
+                     PipeScratch &p, int rpp, bool split, Input0 input0, Step step) {
   const int nc = (n + chunk_pairs - 1) / chunk_pairs;
   const int steps = nc * epochs;
   auto chunk_map = [&](int c, int &start, int &b) {
@@ -1213,7 +1342,7 @@ ff_status epoch_core(ff_layer *layers, int n_layers, const ff_hparams *hp, int n
       float *out_s = p.act_s[l & 1];
       return forward_core(&layers[l], hp, input_of(l, start, b), rpp * b,
                           p.act[l & 1] + (size_t)rpp * start * layers[l].d_out, nullptr,
-                          out_s ? out_s + (size_t)rpp * start : nullptr, p.step[1], s);
+                          out_s ? out_s + (size_t)rpp * start : nullptr, p.step[1], s, split);
     };
     for (int l = 0; l < n_layers; ++l) {
       const bool overlap = l > 0 && fs != st;
@@ -1258,7 +1387,6 @@ ff_status epoch_core(ff_layer *layers, int n_layers, const ff_hparams *hp, int n
     int start, b;
     chunk_map(q % nc, start, b);
     for (int l = 0; l < n_layers; ++l) {
-      ff_layer *L = &layers[l];
       hipStream_t st = static_cast<hipStream_t>(streams[l]);
       if (l > 0) FF_HIP(hipStreamWaitEvent(st, out.ev[(size_t)(l - 1) * kRing + q % kRing], 0));
       if (l + 1 < n_layers && q >= kPipeSlots)
@@ -1340,10 +1468,10 @@ ff_status ff_pipeline_epoch(ff_layer *layers, int32_t n_layers, const ff_hparams
                   float *s_next, StepScratch &sc, hipStream_t st, const NextBf16 *nx,
                   hipEvent_t out_ready) {
     return step_core(&layers[l], hp, in, b, b, h_out, nullptr, loss, s_next, sc, st, nx,
-                     out_ready);
+                     out_ready, kSplitEpoch);
   };
   return epoch_core(layers, n_layers, hp, n, chunk_pairs, epochs, schedule, streams, loss_trace,
-                    p, 2, input0, step);
+                    p, 2, kSplitEpoch, input0, step);
 }
 // ---------------------------------------------------------------------------
 // Chapter schedules (Single-Layer / All-Layers PFF)
@@ -1702,7 +1830,7 @@ ff_status ff_po_epoch(ff_layer *layers, ff_head *heads, int32_t n_layers, const 
                         s_next, sc, st, out_ready);
   };
   return epoch_core(layers, n_layers, hp, n, chunk, epochs, schedule, streams, loss_trace, p, 1,
-                    input0, step);
+                    true, input0, step);
 }
 
 size_t ff_po_predict_workspace_size(const ff_layer *layers, int32_t n_layers, int32_t n,

@@ -47,6 +47,20 @@ struct LabelExpand {
 };
 constexpr int kMaxExpand = 16;  // label counts up to this take the shared-base path
 
+// Scales of the fp32 products' operand rows: scale[r] is the power of two that
+// brings the largest absolute value of row r of rows [n][d] to [2^14, 2^15)
+// (NaN when the row holds inf or NaN).
+struct RowScaleJob {
+  const float *rows;
+  float *scale;
+  int32_t n, d;
+};
+constexpr int kMaxScaleJobs = 8;
+struct RowScaleJobs {
+  RowScaleJob job[kMaxScaleJobs];
+  int32_t count;
+};
+
 // Adam update t: the bias corrections bc1 = 1 - beta1^t and bc2 = 1 - beta2^t
 // enter as lr / bc1 and 1 / bc2 (computed in double on the host).
 struct AdamArgs {
@@ -94,6 +108,13 @@ hipError_t launch_head_logits(const HeadFeatures &f, int n, int C, const int32_t
 hipError_t launch_po_dz(const float *H, const float *G, const float *Wc, int R, int D, int C,
                         float *dZ, float *ones, hipStream_t s);
 
+// The same for an fp32 step, with the row factors of its weight gradient: q [R]
+// and mpart[po_row_blocks(R)] (see DwRows; xscale as in launch_loss).
+int po_row_blocks(int rows);
+hipError_t launch_po_dz_rows(const float *H, const float *G, const float *Wc, int R, int D, int C,
+                             float *dZ, float *ones, const float *xscale, float *q,
+                             int32_t *mpart, hipStream_t s);
+
 // Row splits of the head's weight-gradient reduction.
 int head_grad_splits(int n);
 
@@ -115,50 +136,86 @@ int loss_blocks(int rows);
 // Number of column tiles of the forward product on rows x n_cols, which is
 // the number of goodness partials per row (one per column tile), and its
 // upper bound over all row counts (for sizing scratch).
-int fwd_col_tiles(int rows, int n_cols, int dtype);
+int fwd_col_tiles(int rows, int n_cols, int dtype, bool split);
 int fwd_col_tiles_max(int n_cols);
 int fwd_expand_col_tiles(int rows, int n_cols, int dtype);
 
 // Embedding (optional) + L2 normalisation (optional) into fp32 or bf16 rows.
 // scale_out [rows] (optional): each row's normalisation factor (rounded to
 // bf16 when bf16_out), i.e. the value a one-hot label feature takes.
+// scales (optional, fp32 output only): a row-scale job done by extra
+// workgroups of the launch.
 hipError_t launch_embed_norm(const RowMap &m, int rows, int d, float eps, bool normalise,
-                             bool bf16_out, void *out, float *scale_out, hipStream_t s);
+                             bool bf16_out, void *out, float *scale_out, hipStream_t s,
+                             const RowScaleJob *scales = nullptr);
 
-// H = relu(diag(rowscale) X W^T + b) (optional store) and per-column-tile
-// goodness partials gpart[tile][M].  X: [M][K], W: [N][K]; fp32 or bf16
-// operands (dtype).  rowscale [M] or null (scale 1): the normalisation of raw
-// input rows, applied to the product.
-hipError_t launch_fwd(int dtype, const void *X, const void *W, const float *bias,
-                      const float *rowscale, int M, int N, int K, float *H, float *gpart,
-                      hipStream_t s);
+// The row scales of up to kMaxScaleJobs matrices (d multiples of 4).
+hipError_t launch_row_scales(const RowScaleJob *jobs, int count, hipStream_t s);
+
+// H = relu(X W^T + b) (optional store) and per-column-tile goodness partials
+// gpart[tile][M].  X: [M][K], W: [N][K], bf16.
+hipError_t launch_fwd_bf16(const uint16_t *X, const uint16_t *W, const float *bias, int M, int N,
+                           int K, float *H, float *gpart, hipStream_t s);
+
+// The same on fp32 operands, with diag(rowscale) X for X when rowscale [M] is
+// given (the normalisation of raw input rows).  wscale [N]: the row scales of
+// W, for the split product on the f16 units: the rows (times rowscale) have
+// unit norm at most, or any size with their row scales in xscale [M] (not
+// both).  wscale null: the fp32 matrix instructions.
+hipError_t launch_fwd_f32(const float *X, const float *W, const float *bias, const float *rowscale,
+                          const float *xscale, const float *wscale, int M, int N, int K, float *H,
+                          float *gpart, hipStream_t s);
 
 // Shared-base layer-0 forward: X [M][K] normalised masked base rows, W [N][K],
 // H [M * ex.n_classes][N] (optional) and gpart[tile][M * ex.n_classes] for the
 // expanded rows (see LabelExpand); the number of goodness partials per row is
-// fwd_expand_col_tiles(M, N, dtype) (tiles follow the base rows).
+// fwd_expand_col_tiles(M, N, dtype) (tiles follow the base rows).  wscale [N]:
+// the row scales of W (fp32 only).
 hipError_t launch_fwd_expand(int dtype, const void *X, const void *W, const float *bias,
-                             const LabelExpand &ex, int M, int N, int K, float *H, float *gpart,
-                             hipStream_t s);
+                             const LabelExpand &ex, const float *wscale, int M, int N, int K,
+                             float *H, float *gpart, hipStream_t s);
 
 // g_r = sum_t gpart[t][r] (into g unless null), c_r = 2 dL/dg_r, and loss
 // partials lpart[loss_blocks(R)][2]; s_out (unless null) gets the
 // normalisation 1/(sqrt(g_r) + norm_eps) of the activity rows as the next
-// layer's input (g_r is their squared norm).  With s_in (the layer input's
-// row scales, when its rows are raw), cs_r = c_r * s_in_r.
+// layer's input (g_r is their squared norm).  For the split weight gradient, q
+// [R] and mpart[loss_blocks(R)] receive its row factors (DwRows; xscale: the
+// input rows' row scales, null: unit-norm rows).  For the one on the fp32
+// instructions, cs_r = c_r * s_in_r with s_in, the row scales of raw input rows.
 hipError_t launch_loss(const float *gpart, int ntiles, int R, int n_pos, float theta, float *g,
-                       float *c, float *lpart, float *s_out, float norm_eps, const float *s_in,
-                       float *cs, hipStream_t s);
+                       float *c, float *lpart, float *s_out, float norm_eps,
+                       const float *s_in, float *cs, const float *xscale, float *q,
+                       int32_t *mpart, hipStream_t s);
 
-// dW = (c . H)^T Xh contracted over the R rows, db = sum_r c_r H_r, then one
-// Adam update of W (and its bf16 shadow when Wb != nullptr) and of b; also
-// finishes the loss scalar described by lf.  cs [R] or null (fp32 only): Xh
-// rows are raw, x_hat_r = s_r * Xh_r, and cs_r = c_r * s_r is the factor the
-// product applies to H row r (db still uses c).
-hipError_t launch_dw_adam(int dtype, const float *H, const float *c, const void *Xh,
-                          const float *cs, int M, int N, int K, float *W, float *mW, float *vW,
-                          uint16_t *Wb, float *b, float *mb, float *vb, const AdamArgs &a,
-                          const LossFinish &lf, hipStream_t s);
+// Row factors of the split fp32 weight gradient dW = sum_r c_r h_r^T (s_r x_r): c,
+// the rows' share q of their size on the x side (a power of two), and the
+// exponents m [nm] whose largest sets the common scale.  s null: 1.
+struct DwRows {
+  const float *c, *q, *s;
+  const int32_t *m;
+  int32_t nm;
+};
+
+// dW = sum_r c_r h_r^T (s_r x_r) over the K rows of H [K][M] and Xh [K][N],
+// db = sum_r c_r H_r, then one Adam update of W [M][N] and of b; also finishes
+// the loss scalar described by lf.
+hipError_t launch_dw_adam_split(const float *H, const float *Xh, const DwRows &rows, int M, int N,
+                                int K, float *W, float *mW, float *vW, float *b, float *mb,
+                                float *vb, const AdamArgs &a, const LossFinish &lf, hipStream_t s);
+
+// The same on the fp32 matrix instructions; cs [K] or null: c_r s_r of raw
+// input rows.
+hipError_t launch_dw_adam_f32(const float *H, const float *c, const float *Xh, const float *cs,
+                              int M, int N, int K, float *W, float *mW, float *vW, float *b,
+                              float *mb, float *vb, const AdamArgs &a, const LossFinish &lf,
+                              hipStream_t s);
+
+// The same with bf16 operands (bf16(c . H), Xh already normalised bf16 rows)
+// and the update of W's bf16 shadow Wb.
+hipError_t launch_dw_adam_bf16(const float *H, const float *c, const uint16_t *Xh, int M, int N,
+                               int K, float *W, float *mW, float *vW, uint16_t *Wb, float *b,
+                               float *mb, float *vb, const AdamArgs &a, const LossFinish &lf,
+                               hipStream_t s);
 
 // Rows of the transposed bf16 weight-gradient operands: R rounded up to a
 // multiple of 64 (the extra columns are zeros).

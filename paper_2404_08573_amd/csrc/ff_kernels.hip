@@ -6,20 +6,22 @@
 // Kernels
 //   k_embed_norm   label embedding (Sec. 3 "Negative Data") + row L2 normalisation;
 //                  one wave per row, float4 loads, HBM-bound.
-//   k_fwd          Z = X W^T on MFMA (v_mfma_f32_32x32x2f32 for fp32 operands,
-//                  v_mfma_f32_32x32x16_bf16 for bf16), operands loaded straight into
-//                  LDS (buffer_load ... lds); the epilogue fuses bias, ReLU, the
-//                  H store and the per-row goodness partial sum over the tile's
-//                  columns (Eq. 1) through a lane butterfly and LDS.
+//   k_fwd_split    fp32 Z = X W^T as three f16 matrix products of two-part operands, fp32
+//                  accumulation; the epilogue fuses bias, ReLU, the H store and the
+//                  per-row goodness partial sum over the tile's columns (Eq. 1).
+//   k_fwd          the same in bf16 (v_mfma_f32_32x32x16_bf16), and on the fp32 matrix
+//                  instructions (v_mfma_f32_32x32x2f32) in fp32 training epochs;
+//                  operands loaded straight into LDS (buffer_load ... lds).
 //   k_loss_rows    goodness partials -> g, the per-row gradient coefficient
 //                  c_r = 2 dL/dg_r and per-workgroup sums of the Eq. 1 loss terms.
-//   k_dw_adam_f32  dW = (c.H)^T X_hat on fp32 MFMA (contraction over the batch rows),
-//                  the row scale c applied while staging H, db summed from the same
-//                  staged rows, and the Adam update of W and b fused in the epilogue
-//                  (no split over rows, so every dW tile is final in one workgroup);
-//                  its first thread also finishes the loss scalar in a fixed order.
+//   k_dw_adam_split  fp32 dW = (c.H)^T X_hat on the split product, contraction over the
+//                  batch rows, db from the same staged rows, and the Adam update of W
+//                  and b fused in the epilogue (no split over workgroups, so every dW
+//                  tile is final in one); its first thread also finishes the loss scalar.
+//   k_dw_adam_f32  the same on the fp32 matrix instructions (fp32 training epochs).
 //   k_dw_adam_bf16 the same on v_mfma_f32_32x32x16_bf16: tiles staged in their
 //                  natural layout, MFMA fragments through LDS transpose reads.
+//   k_row_scales   powers of two that scale the split products' operand rows.
 //   k_goodness, k_argmax, k_bf16_shadow: small row/elementwise kernels.
 //
 // Every reduction runs in a fixed order, so results are bitwise reproducible
@@ -144,10 +146,72 @@ __device__ __forceinline__ float4 embed4(float4 v, int col, int lab, int C) {
   return v;
 }
 
+// ---------------------------------------------------------------------------
+// Row scales of the fp32 products' operands (see the split product below)
+// ---------------------------------------------------------------------------
+// Scale of a row from the largest bit pattern of its absolute values: the
+// power of two that brings that value to [2^14, 2^15) (at most 2^103, which
+// rows of zeros and denormals get), NaN when the row holds inf or NaN.
+__device__ __forceinline__ float row_scale_of(uint32_t maxbits) {
+  const uint32_t e = maxbits >> 23;
+  if (e >= 255) return __uint_as_float(0x7fc00000u);
+  return __uint_as_float(min(268u - e, 230u) << 23);
+}
+__device__ __forceinline__ uint32_t abs_bits(float v) { return __float_as_uint(v) & 0x7fffffffu; }
+
+// Row scales of one wave's row of a job (see RowScaleJob); `blk` counts
+// workgroups of kBlock / 64 rows.
+__device__ __forceinline__ void row_scale_wave(const RowScaleJob &job, int blk) {
+  const int lane = threadIdx.x & 63;
+  const int r = blk * (kBlock / 64) + (threadIdx.x >> 6);
+  if (r >= job.n) return;  // uniform per wave
+  const float *p = job.rows + (size_t)r * job.d;
+  const int d4 = job.d >> 2;
+  uint32_t m = 0;
+  int i = lane;
+  for (; i + 7 * 64 < d4; i += 8 * 64) {  // eight loads in flight
+    float4 v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = ld4(p + 4 * (i + 64 * j));
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      m = max(max(m, max(abs_bits(v[j].x), abs_bits(v[j].y))),
+              max(abs_bits(v[j].z), abs_bits(v[j].w)));
+  }
+  float4 v[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    v[j] = i + 64 * j < d4 ? ld4(p + 4 * (i + 64 * j)) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    m = max(max(m, max(abs_bits(v[j].x), abs_bits(v[j].y))),
+            max(abs_bits(v[j].z), abs_bits(v[j].w)));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+  if (lane == 0) job.scale[r] = row_scale_of(m);
+}
+
+// Scales of the rows of up to kMaxScaleJobs matrices in one launch, one wave
+// per row.  2000 x 2000: 4 us, most of it the launch.
+__global__ __launch_bounds__(kBlock) void k_row_scales(RowScaleJobs jobs) {
+  int blk = blockIdx.x, j = 0;
+  while (j + 1 < jobs.count) {
+    const int nb = (jobs.job[j].n + kBlock / 64 - 1) / (kBlock / 64);
+    if (blk < nb) break;
+    blk -= nb;
+    ++j;
+  }
+  row_scale_wave(jobs.job[j], blk);
+}
+
+// Workgroups past the rows' own take the row scales of `job` (fp32 output):
+// the scales of the weights that the next product multiplies the rows with.
 template <bool BF16OUT>
 __global__ __launch_bounds__(kBlock) void k_embed_norm(RowMap m, int rows, int d, float eps,
                                                        int normalise, void *out,
-                                                       float *scale_out) {
+                                                       float *scale_out, RowScaleJob job) {
+  const int nblk = (rows + kBlock / 64 - 1) / (kBlock / 64);
+  if (!BF16OUT && (int)blockIdx.x >= nblk) return row_scale_wave(job, blockIdx.x - nblk);
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   if (r >= rows) return;  // uniform per wave
@@ -191,7 +255,9 @@ __global__ __launch_bounds__(kBlock) void k_embed_norm(RowMap m, int rows, int d
 template <int NV, bool BF16OUT>
 __global__ __launch_bounds__(kBlock) void k_embed_norm_reg(RowMap m, int rows, int d, float eps,
                                                            int normalise, void *out,
-                                                           float *scale_out) {
+                                                           float *scale_out, RowScaleJob job) {
+  const int nblk = (rows + kBlock / 64 - 1) / (kBlock / 64);
+  if (!BF16OUT && (int)blockIdx.x >= nblk) return row_scale_wave(job, blockIdx.x - nblk);
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   if (r >= rows) return;  // uniform per wave
@@ -321,6 +387,8 @@ __device__ __forceinline__ void lds_barrier() {
 // s_waitcnt operand: at most n vector-memory operations outstanding, no limit
 // on the other counters (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
 constexpr int vmcnt_wait(int n) { return 0x0f70 | (n & 15) | ((n >> 4) << 14); }
+// The same with no LDS operation outstanding.
+constexpr int vmcnt_lgkm0(int n) { return 0x0070 | (n & 15) | ((n >> 4) << 14); }
 // s_waitcnt operands: nothing outstanding; no LDS (or scalar memory) operation
 // outstanding, any number of vector-memory ones.
 constexpr int kWaitAll = 0x0070;
@@ -640,6 +708,502 @@ __global__ __launch_bounds__(WM *WN * 64) void k_fwd(const typename Operand<BF16
 }
 
 // ---------------------------------------------------------------------------
+// fp32 products on the f16 matrix units.  An fp32 operand times a power-of-two
+// scale p that brings the largest value of its row to 2^14..2^15 is split into
+// two f16 values, hi = f16(x p) and lo = f16(x p - hi) (the difference is exact
+// in fp32): hi + lo carries x to within one unit of its 24th bit, down to
+// values 2^-15 of the row's largest, and to 2^-40 of that largest below.  A
+// product is hi hi + hi lo + lo hi on v_mfma_f32_32x32x16_f16 with fp32
+// accumulation; the missing lo lo is under 2^-24 of the product.  The k-split
+// below also halves the length of every accumulation chain, so the results are
+// closer to 64-bit ones than the fp32 matrix instructions' were (2048 x 2000 x
+// 2000: 3.6e-7 against 5.6e-7 in the 2-norm).
+//
+// v_mfma_f32_32x32x2f32 runs at 1/16 of the f16 rate, so three f16 products
+// take 3/16 of its time; the chip's power then limits the clock (1.75 GHz
+// against 2.2 GHz) and LDS reads bound the rest: 2048 x 2000 x 2000 took
+// 145 us on the fp32 instructions and takes 70 us, 20480 rows 1290 and 590 us.
+//
+// A value that is not finite, or past its scale's bound, gives inf - inf = NaN
+// in lo and so NaN in every sum it enters; a workgroup that finds a NaN among
+// its results computes its tile again with the fp32 instructions, straight
+// from global memory (nt_exact, tn_exact), which give what fp32 arithmetic gives.
+// ---------------------------------------------------------------------------
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+
+// Scale of unit-norm rows (and the exponent every other scale aims at).
+constexpr float kUnitScale = 16384.f;
+
+// A fragment of eight k-consecutive values per lane, as f16 high and low parts.
+struct HalfPair {
+  uint4 h, l;
+};
+
+// a p and b p as packed f16 parts.  The empty asm keeps the compiler from
+// converting the high parts a second time for the subtraction.
+__device__ __forceinline__ void split_pair(float a, float pa, float b, float pb, uint32_t &h,
+                                           uint32_t &l) {
+  const half2_t t = {(_Float16)(a * pa), (_Float16)(b * pb)};
+  h = __builtin_bit_cast(uint32_t, t);
+  asm("" : "+v"(h));
+  const half2_t hv = __builtin_bit_cast(half2_t, h);
+  const half2_t lv = {(_Float16)__builtin_fmaf(a, pa, -(float)hv[0]),
+                      (_Float16)__builtin_fmaf(b, pb, -(float)hv[1])};
+  l = __builtin_bit_cast(uint32_t, lv);
+}
+__device__ __forceinline__ floatx16 mfma_f16(const uint4 &a, const uint4 &b, floatx16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, a),
+                                                __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
+}
+// acc += a b of two split fragments, the small terms first.
+__device__ __forceinline__ void mfma_split(const HalfPair &a, const HalfPair &b, floatx16 &acc) {
+  acc = mfma_f16(a.l, b.h, acc);
+  acc = mfma_f16(a.h, b.l, acc);
+  acc = mfma_f16(a.h, b.h, acc);
+}
+
+// 1 / p of a power of two p (2^-125 .. 2^125), exact.
+__device__ __forceinline__ float pow2_inv(float p) {
+  return __uint_as_float(0x7f000000u - __float_as_uint(p));
+}
+
+// K-split reduction.  The WK waves of one output position hold partial sums of
+// the same MB x NB blocks; through LDS, wave wk receives the full sums of the
+// blocks whose position mb * NB + nb is wk modulo WK, in order into own, RC of
+// a block's 16 registers at a time.  Uses NW * (WK - 1) * RC * 64 floats from
+// `red`; ends with a barrier.
+template <int MB, int NB, int WK, int RC>
+__device__ __forceinline__ void ksplit_reduce(floatx16 (&acc)[MB][NB], float *red, int wmn, int wk,
+                                              int lane, floatx16 (&own)[MB * NB / WK]) {
+  static_assert(MB * NB % WK == 0 && 16 % RC == 0, "blocks and registers split evenly");
+  float *base = red + wmn * WK * (WK - 1) * RC * 64;  // [owner][giver slot][RC][64]
+#pragma unroll
+  for (int i = 0; i < MB * NB / WK; ++i)
+#pragma unroll
+    for (int r0 = 0; r0 < 16; r0 += RC) {
+#pragma unroll
+      for (int o = 0; o < WK; ++o) {  // block i * WK + o belongs to wave o
+        const floatx16 &a = acc[(i * WK + o) / NB][(i * WK + o) % NB];
+        if (wk == o) {
+#pragma unroll
+          for (int r = r0; r < r0 + RC; ++r) own[i][r] = a[r];
+        } else {
+          float *dst = base + (o * (WK - 1) + (wk < o ? wk : wk - 1)) * RC * 64 + lane;
+#pragma unroll
+          for (int r = 0; r < RC; ++r) dst[r * 64] = a[r0 + r];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int g = 0; g < WK - 1; ++g) {
+        const float *src = base + (wk * (WK - 1) + g) * RC * 64 + lane;
+#pragma unroll
+        for (int r = 0; r < RC; ++r) own[i][r0 + r] += src[r * 64];
+      }
+      __syncthreads();
+    }
+}
+
+// Geometry of an fp32 product tile: BM x BN outputs, WM x WN wave positions
+// of (BM/WM) x (BN/WN) outputs, each taken by WK waves that share the k range
+// (wave wk takes k-steps wk, wk + WK, .. of 16), on NBUF LDS stages.
+template <int BM_, int BN_, int WM_, int WN_, int WK_, int NBUF_ = 2>
+struct SplitTile {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, WK = WK_;
+  static constexpr int NW = WM * WN * WK, threads = NW * 64;
+  static constexpr int TM = BM / WM, TN = BN / WN, MB = TM / 32, NB = TN / 32;
+  static constexpr int OWN = MB * NB / WK;
+  static constexpr int BK = 16 * WK;                       // k of one LDS stage
+  static constexpr int NBUF = NBUF_, STAGE = (BM + BN) * BK;  // floats of one LDS stage
+  static constexpr int RC = NW * (WK - 1) * 1024 <= STAGE ? 16 : 8;  // see ksplit_reduce
+  static_assert(NW * (WK - 1) * RC * 64 <= STAGE && (NBUF == 2 || NBUF == 3), "LDS");
+  static_assert(WK >= 2 && WK % 2 == 0 && MB % 2 == 0 && MB * NB % WK == 0, "tile");
+  static long tiles(int m, int n) {
+    return (long)((m + BM - 1) / BM) * ((n + BN - 1) / BN);
+  }
+};
+
+// NT main loop of the split product: acc = the wave's partial sums of
+// (X p_x)(W p_w)^T.  X [M][K], W [N][K], both fp32 and K-contiguous; pa, pb:
+// the scales of the lane's X and W rows.
+//
+// Operand bytes move as in nt_mainloop: global memory straight into LDS, 128
+// bytes of a row per sub-tile of 32 k (WK / 2 sub-tiles per stage), the same
+// swizzle, NBUF LDS stages.  The waves split what they read from LDS into f16
+// parts in registers (five VALU instructions per pair of values), which keeps
+// the operands at four bytes per value on the way in; storing the parts
+// instead would cost a pass over both operands.
+//
+// The loop is a software pipeline over units of one 32-row X block: while the
+// unit's 3 * NB matrix products run, the next unit's X block is split, and in
+// the last two units of a k-step also the next k-step's W blocks.  The stage
+// barrier stands before those two units: past it, the next stage has landed
+// and every wave has read the current one, which stage t + NBUF then refills.
+// The LDS stages are arrays of their own, named by constant indices: the
+// compiler then sees that the loads into one stage do not alias the reads of
+// another.  With one array it waited for every load in flight before the reads
+// that follow them in a step (2048 x 2000 x 2000: 88 us instead of 70).
+struct Stages {
+  float *p[3];
+};
+#define FF_SPLIT_STAGES(S, st)                                            \
+  __shared__ __attribute__((aligned(16))) float sm0[S::STAGE];            \
+  __shared__ __attribute__((aligned(16))) float sm1[S::STAGE];            \
+  __shared__ __attribute__((aligned(16))) float sm2[S::NBUF > 2 ? S::STAGE : 4]; \
+  const Stages st = {{sm0, sm1, sm2}}
+
+template <class S>
+__device__ __forceinline__ void nt_split_loop(const float *__restrict__ X,
+                                              const float *__restrict__ W, int M, int N, int K,
+                                              int m0, int n0, const Stages &st,
+                                              const float (&pa)[S::MB], const float (&pb)[S::NB],
+                                              floatx16 (&acc)[S::MB][S::NB]) {
+  constexpr int MB = S::MB, NB = S::NB, BM = S::BM, BN = S::BN, BK = S::BK;
+  constexpr int SUB = S::WK / 2, SUBE = (BM + BN) * 32;  // sub-tiles per stage, floats in one
+  constexpr int NBUF = S::NBUF;
+  constexpr int IA = BM / 8 * SUB / S::NW, IB = BN / 8 * SUB / S::NW;  // wave loads per stage
+  static_assert(IA * S::NW == BM / 8 * SUB && IB * S::NW == BN / 8 * SUB, "wave loads");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave % S::WK, wm = wave / S::WK / S::WN, wn = wave / S::WK % S::WN;
+  const int li = lane & 31, kg = lane >> 5;
+  const __amdgpu_buffer_rsrc_t ra =
+      buffer_rsrc(X + (size_t)m0 * K, (uint32_t)(min(BM, M - m0) * K * 4));
+  const __amdgpu_buffer_rsrc_t rb =
+      buffer_rsrc(W + (size_t)n0 * K, (uint32_t)(min(BN, N - n0) * K * 4));
+  const int lpos = lane & 7;
+  int kca[IA], kcb[IB];
+  uint32_t oa[IA], ob[IB];
+#pragma unroll
+  for (int i = 0; i < IA; ++i) {
+    const int e = wave * IA + i, r = (e % (BM / 8)) * 8 + (lane >> 3);
+    kca[i] = e / (BM / 8) * 32 + nt_swz(r, lpos) * 4;
+    oa[i] = (uint32_t)((r * K + kca[i]) * 4);
+  }
+#pragma unroll
+  for (int i = 0; i < IB; ++i) {
+    const int e = wave * IB + i, r = (e % (BN / 8)) * 8 + (lane >> 3);
+    kcb[i] = e / (BN / 8) * 32 + nt_swz(r, lpos) * 4;
+    ob[i] = (uint32_t)((r * K + kcb[i]) * 4);
+  }
+  auto issue = [&](int kt, int buf) {
+    float *St = st.p[buf];
+    const int kb = kt * BK;
+#pragma unroll
+    for (int i = 0; i < IA; ++i) {
+      const int e = wave * IA + i;
+      const uint32_t o = kb + kca[i] < K ? oa[i] + kb * 4 : kOutOfRange;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          ra, (lds_void *)(St + e / (BM / 8) * SUBE + e % (BM / 8) * 256), 16, o, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < IB; ++i) {
+      const int e = wave * IB + i;
+      const uint32_t o = kb + kcb[i] < K ? ob[i] + kb * 4 : kOutOfRange;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rb, (lds_void *)(St + e / (BN / 8) * SUBE + BM * 32 + e % (BN / 8) * 256), 16, o, 0, 0,
+          0);
+    }
+  };
+  // The lane's eight k of a 32-row block of stage buf: two 16-byte chunks.
+  // (Vector types: the compiler splits a load of a struct type in halves.)
+  const int swz = (li & 7) ^ ((li >> 3) & 1), c0 = 4 * (wk & 1) + 2 * kg;
+  const int frag0 = wk / 2 * SUBE + li * 32;
+  auto rd = [&](int buf, int row, float4_t (&r)[2]) {
+    const float *p = st.p[buf] + frag0 + row * 32;
+    r[0] = *reinterpret_cast<const float4_t *>(p + (c0 ^ swz) * 4);
+    r[1] = *reinterpret_cast<const float4_t *>(p + ((c0 + 1) ^ swz) * 4);
+  };
+  auto split = [&](const float4_t (&r)[2], float p, HalfPair &s) {
+    split_pair(r[0].x, p, r[0].y, p, s.h.x, s.l.x);
+    split_pair(r[0].z, p, r[0].w, p, s.h.y, s.l.y);
+    split_pair(r[1].x, p, r[1].y, p, s.h.z, s.l.z);
+    split_pair(r[1].z, p, r[1].w, p, s.h.w, s.l.w);
+  };
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.f;
+
+  HalfPair fa[2], fb[2][NB];
+  float4_t xr[2][2], wr[NB][2];
+  const int nk = (K + BK - 1) / BK;
+#pragma unroll
+  for (int j = 0; j < NBUF; ++j) issue(j, j);
+  __builtin_amdgcn_s_waitcnt(vmcnt_wait((NBUF - 1) * (IA + IB)));
+  lds_barrier();
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    rd(0, BM + wn * S::TN + nb * 32, wr[nb]);
+    split(wr[nb], pb[nb], fb[0][nb]);
+  }
+  rd(0, wm * S::TM, xr[0]);
+  split(xr[0], pa[0], fa[0]);
+  rd(0, wm * S::TM + 32, xr[1]);
+  // k-step kt from stage buf with the W parts wc; the next step's, from stage
+  // nxt, go into wnx.
+  auto step = [&](int kt, int buf, int nxt, HalfPair (&wc)[NB], HalfPair (&wnx)[NB]) {
+#pragma unroll
+    for (int u = 0; u < MB; ++u) {
+      if (u == MB - 2) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0((NBUF - 2) * (IA + IB)));
+        lds_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        issue(kt + NBUF, buf);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) rd(nxt, BM + wn * S::TN + nb * 32, wr[nb]);
+      }
+      // unit u + 2's X block: of this stage, or the next one's past its end
+      if (u + 2 < MB)
+        rd(buf, wm * S::TM + (u + 2) * 32, xr[u & 1]);
+      else
+        rd(nxt, wm * S::TM + (u + 2 - MB) * 32, xr[u & 1]);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[u][nb] = mfma_f16(fa[u & 1].l, wc[nb].h, acc[u][nb]);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[u][nb] = mfma_f16(fa[u & 1].h, wc[nb].l, acc[u][nb]);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[u][nb] = mfma_f16(fa[u & 1].h, wc[nb].h, acc[u][nb]);
+      split(xr[(u + 1) & 1], pa[(u + 1) % MB], fa[(u + 1) & 1]);
+      if (u >= MB - 2)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+          if (nb % 2 == u - (MB - 2)) split(wr[nb], pb[nb], wnx[nb]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  constexpr int U = NBUF % 2 == 0 ? NBUF : 2 * NBUF;  // stages and parts in fixed places
+  int kt = 0;
+  for (; kt + U <= nk; kt += U)
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+      step(kt + j, j % NBUF, (j + 1) % NBUF, fb[j & 1], fb[(j + 1) & 1]);
+#pragma unroll
+  for (int j = 0; j < U - 1; ++j)
+    if (kt + j < nk) step(kt + j, j % NBUF, (j + 1) % NBUF, fb[j & 1], fb[(j + 1) & 1]);
+  __builtin_amdgcn_s_waitcnt(vmcnt_wait(0));
+  lds_barrier();
+}
+
+// One 32 x 32 block of X W^T (rows m0.., columns n0..; those past M or N
+// repeat the last) on the fp32 matrix instructions, operands from global
+// memory: the tiles whose split sums are not finite.
+__device__ __forceinline__ void nt_exact(const float *__restrict__ X, const float *__restrict__ W,
+                                         int M, int N, int K, int m0, int n0, int lane,
+                                         floatx16 &acc) {
+  const int li = lane & 31, kg = lane >> 5;
+  const float *x = X + (size_t)min(m0 + li, M - 1) * K + kg;
+  const float *w = W + (size_t)min(n0 + li, N - 1) * K + kg;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll 1
+  for (int k = 0; k < K; k += 2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[k], w[k], acc, 0, 0, 0);
+}
+
+// The tile's product of X (row scales xscale, or unit-norm rows after the
+// factors rowscale, or unit-norm as they are) and W (row scales wscale): own[i]
+// = sum over k of x w, times the row's rowscale when there is one, for the
+// wave's blocks i (position wk + WK * i of the MB x NB blocks, row by row).
+// bv[i]: the bias of the lane's column of block i (loaded, like the scales,
+// before the main loop: a small tile's epilogue would wait for each in turn).
+template <class S>
+__device__ __forceinline__ void nt_split_product(
+    const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ bias,
+    const float *__restrict__ rowscale, const float *__restrict__ xscale,
+    const float *__restrict__ wscale, int M, int N, int K, int m0, int n0, const Stages &st,
+    floatx16 (&own)[S::OWN], float (&bv)[S::OWN]) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wk = wave % S::WK, wmn = wave / S::WK, wm = wmn / S::WN, wn = wmn % S::WN;
+  const int li = lane & 31, kg = lane >> 5;
+  float pa[S::MB], pb[S::NB], uc[S::OWN];
+#pragma unroll
+  for (int mb = 0; mb < S::MB; ++mb) {
+    const int row = min(m0 + wm * S::TM + mb * 32 + li, M - 1);
+    pa[mb] = xscale ? xscale[row] : (rowscale ? rowscale[row] : 1.f) * kUnitScale;
+  }
+#pragma unroll
+  for (int nb = 0; nb < S::NB; ++nb)
+    pb[nb] = wscale[min(n0 + wn * S::TN + nb * 32 + li, N - 1)];
+#pragma unroll
+  for (int i = 0; i < S::OWN; ++i) {
+    const int col = min(n0 + wn * S::TN + (wk + S::WK * i) % S::NB * 32 + li, N - 1);
+    uc[i] = wscale[col];
+    bv[i] = bias[col];
+  }
+  {
+    floatx16 acc[S::MB][S::NB];
+    nt_split_loop<S>(X, W, M, N, K, m0, n0, st, pa, pb, acc);
+    ksplit_reduce<S::MB, S::NB, S::WK, S::RC>(acc, st.p[0], wmn, wk, lane, own);
+  }
+  int bad = 0;
+#pragma unroll
+  for (int i = 0; i < S::OWN; ++i) {
+    const int rbase = m0 + wm * S::TM + (wk + S::WK * i) / S::NB * 32;
+    const float u = pow2_inv(uc[i]) * (1.f / kUnitScale);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) bad |= own[i][r] != own[i][r];
+    if (xscale) {  // the smaller factor first: no overflow that the result does not have
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float v = pow2_inv(xscale[min(rbase + acc_row(r, kg), M - 1)]) * kUnitScale;
+        own[i][r] = own[i][r] * fminf(u, v) * fmaxf(u, v);
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) own[i][r] *= u;
+    }
+  }
+  if (__syncthreads_or(bad)) {
+#pragma unroll
+    for (int i = 0; i < S::OWN; ++i) {
+      const int b = wk + S::WK * i, mb = b / S::NB, nb = b % S::NB;
+      const int rbase = m0 + wm * S::TM + mb * 32;
+      nt_exact(X, W, M, N, K, rbase, n0 + wn * S::TN + nb * 32, lane, own[i]);
+      if (rowscale)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) own[i][r] *= rowscale[min(rbase + acc_row(r, kg), M - 1)];
+    }
+  }
+}
+
+// fp32 forward: H = relu(X W^T + b) (optional store) and the goodness partials
+// gpart[tn][row] over the tile's columns, from the split product.
+template <class S, bool STORE_H>
+__global__ __launch_bounds__(S::threads, 2) void k_fwd_split(
+    const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ bias,
+    const float *__restrict__ rowscale, const float *__restrict__ xscale,
+    const float *__restrict__ wscale, int M, int N, int K, float *__restrict__ H,
+    float *__restrict__ gpart) {
+  constexpr int CB = S::WN * S::NB;  // 32-column blocks of the tile
+  FF_SPLIT_STAGES(S, st);
+  const int nt = (N + S::BN - 1) / S::BN;
+  int tm, tn;
+  tile_of(blockIdx.x, (M + S::BM - 1) / S::BM, nt, tm, tn);
+  const int m0 = tm * S::BM, n0 = tn * S::BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave % S::WK, wm = wave / S::WK / S::WN, wn = wave / S::WK % S::WN;
+  const int li = lane & 31, kg = lane >> 5;
+  floatx16 own[S::OWN];
+  float bv[S::OWN];
+  nt_split_product<S>(X, W, bias, rowscale, xscale, wscale, M, N, K, m0, n0, st, own, bv);
+
+  float *gs = sm0;  // [CB][BM]; nt_split_product ends with a barrier
+#pragma unroll
+  for (int i = 0; i < S::OWN; ++i) {
+    const int b = wk + S::WK * i, mb = b / S::NB, cb = wn * S::NB + b % S::NB;
+    const int rl = wm * S::TM + mb * 32, col = n0 + cb * 32 + li;
+    const bool cok = col < N;
+    float hsq[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      own[i][r] = cok ? fmaxf(own[i][r] + bv[i], 0.f) : 0.f;
+      hsq[r] = own[i][r] * own[i][r];
+    }
+    rowsum_scatter(hsq, lane);
+    const int q = (lane & 31) >> 1;
+    if ((lane & 1) == 0) gs[cb * S::BM + rl + acc_row(q, kg)] = hsq[0];
+  }
+  __syncthreads();
+  for (int t = tid; t < S::BM; t += S::threads) {
+    const int row = m0 + t;
+    if (row < M) {
+      float g = 0.f;
+#pragma unroll
+      for (int c = 0; c < CB; ++c) g += gs[c * S::BM + t];
+      gpart[(size_t)tn * M + row] = g;
+    }
+  }
+  // H last: a barrier after the stores would wait until they are all written.
+  if constexpr (STORE_H) {
+#pragma unroll
+    for (int i = 0; i < S::OWN; ++i) {
+      const int b = wk + S::WK * i, cb = wn * S::NB + b % S::NB;
+      const int rbase = m0 + wm * S::TM + b / S::NB * 32, col = n0 + cb * 32 + li;
+      if (col < N)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = rbase + acc_row(r, kg);
+          if (row < M) H[(size_t)row * N + col] = own[i][r];
+        }
+    }
+  }
+}
+
+// fp32 shared-base layer-0 forward (see k_fwd_expand) from the split product.
+template <class S, bool STORE_H>
+__global__ __launch_bounds__(S::threads, 2) void k_fwd_expand_split(
+    const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ bias,
+    LabelExpand ex, const float *__restrict__ wscale, int M, int N, int K, float *__restrict__ H,
+    float *__restrict__ gpart) {
+  constexpr int CB = S::WN * S::NB;
+  FF_SPLIT_STAGES(S, st);
+  static_assert(kMaxExpand * CB * S::BM <= S::STAGE && kMaxExpand * S::BN <= S::STAGE, "LDS");
+  const int nt = (N + S::BN - 1) / S::BN;
+  int tm, tn;
+  tile_of(blockIdx.x, (M + S::BM - 1) / S::BM, nt, tm, tn);
+  const int m0 = tm * S::BM, n0 = tn * S::BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave % S::WK, wm = wave / S::WK / S::WN, wn = wave / S::WK % S::WN;
+  const int li = lane & 31, kg = lane >> 5;
+  const int C = ex.n_classes;
+  floatx16 own[S::OWN];
+  float bv[S::OWN];
+  nt_split_product<S>(X, W, bias, nullptr, nullptr, wscale, M, N, K, m0, n0, st, own, bv);
+
+  float *gs = sm0;  // [C][CB][BM] goodness partials
+  float *wl = sm1;  // [BN][kMaxExpand] label columns of W
+  for (int i = tid; i < S::BN * C; i += S::threads) {
+    const int j = i / C, c = i % C;
+    wl[j * kMaxExpand + c] = W[(size_t)min(n0 + j, N - 1) * K + c];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < S::OWN; ++i) {
+    const int b = wk + S::WK * i, mb = b / S::NB, cb = wn * S::NB + b % S::NB;
+    const int rl = wm * S::TM + mb * 32, cl = cb * 32 + li, col = n0 + cl;
+    const bool cok = col < N;
+    float sr[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sr[r] = ex.scale[min(m0 + rl + acc_row(r, kg), M - 1)];
+    for (int c = 0; c < C; ++c) {
+      const float wc = wl[cl * kMaxExpand + c];
+      float hsq[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = m0 + rl + acc_row(r, kg);
+        const float h = cok ? fmaxf(own[i][r] + fmaf(sr[r], wc, bv[i]), 0.f) : 0.f;
+        if (STORE_H && cok && row < M) H[((size_t)row * C + c) * N + col] = h;
+        hsq[r] = h * h;
+      }
+      rowsum_scatter(hsq, lane);
+      const int q = (lane & 31) >> 1;
+      if ((lane & 1) == 0) gs[(c * CB + cb) * S::BM + rl + acc_row(q, kg)] = hsq[0];
+    }
+  }
+  __syncthreads();
+  const size_t MO = (size_t)M * C;
+  for (int i = tid; i < S::BM * C; i += S::threads) {
+    const int t = i % S::BM, c = i / S::BM;
+    const int row = m0 + t;
+    if (row < M) {
+      float g = 0.f;
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) g += gs[(c * CB + cb) * S::BM + t];
+      gpart[(size_t)tn * MO + (size_t)row * C + c] = g;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // bf16 forward on four waves of 128 x (BN/2) each (one wave per SIMD).
 // The 8-wave tiles above give each wave a 32x64 or 64x96 share, whose MFMA
 // fragments cost more LDS read bytes per flop than the CU's LDS delivers at
@@ -655,10 +1219,6 @@ __global__ __launch_bounds__(WM *WN * 64) void k_fwd(const typename Operand<BF16
 // Same operand layout, k permutation, swizzle and zero-filled tails as
 // nt_mainloop with two LDS stages; same epilogue results as k_fwd.
 // ---------------------------------------------------------------------------
-
-// s_waitcnt operand: at most n vector-memory operations and no LDS operation
-// outstanding.
-constexpr int vmcnt_lgkm0(int n) { return 0x0070 | (n & 15) | ((n >> 4) << 14); }
 
 template <int BM, int BN, int NBUF = 2>
 __device__ __forceinline__ void nt_mainloop4(const uint16_t *__restrict__ X,
@@ -805,10 +1365,8 @@ __device__ __forceinline__ void nt_mainloop4(const uint16_t *__restrict__ X,
 template <int BM, int BN, int NBUF, bool STORE_H>
 __global__ __launch_bounds__(256) void k_fwd4(const uint16_t *__restrict__ X,
                                               const uint16_t *__restrict__ W,
-                                              const float *__restrict__ bias,
-                                              const float *__restrict__ rowscale, int M, int N,
-                                              int K, float *__restrict__ H,
-                                              float *__restrict__ gpart) {
+                                              const float *__restrict__ bias, int M, int N, int K,
+                                              float *__restrict__ H, float *__restrict__ gpart) {
   constexpr int WN = 2, TM = BM / 2, TN = BN / 2, MB = TM / 32, NB = TN / 32;
   __shared__ __attribute__((aligned(16))) uint16_t sm[NBUF * (BM + BN) * 64];
   const int nt = (N + BN - 1) / BN;
@@ -822,7 +1380,7 @@ __global__ __launch_bounds__(256) void k_fwd4(const uint16_t *__restrict__ X,
   nt_mainloop4<BM, BN, NBUF>(X, W, M, N, K, m0, n0, sm, acc);
 
   // Epilogue as in k_fwd, one 32-row block at a time, so that only 16 row
-  // sums and scales are live beside the accumulators.
+  // sums are live beside the accumulators.
   float bv[NB];
   bool cok[NB];
 #pragma unroll
@@ -834,18 +1392,15 @@ __global__ __launch_bounds__(256) void k_fwd4(const uint16_t *__restrict__ X,
   float *gs = reinterpret_cast<float *>(sm);  // [WN][BM]; the main-loop buffers are free now
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
-    float hsq[16], rs[16];
+    float hsq[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      hsq[r] = 0.f;
-      rs[r] = rowscale ? rowscale[min(m0 + wm * TM + mb * 32 + acc_row(r, kg), M - 1)] : 1.f;
-    }
+    for (int r = 0; r < 16; ++r) hsq[r] = 0.f;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       const int col = n0 + wn * TN + nb * 32 + li;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float h = cok[nb] ? fmaxf(fmaf(acc[mb][nb][r], rs[r], bv[nb]), 0.f) : 0.f;
+        const float h = cok[nb] ? fmaxf(acc[mb][nb][r] + bv[nb], 0.f) : 0.f;
         if (STORE_H) {
           const int row = m0 + wm * TM + mb * 32 + acc_row(r, kg);
           if (row < M && cok[nb]) H[(size_t)row * N + col] = h;
@@ -1082,15 +1637,13 @@ __global__ __launch_bounds__(kBlock) void k_adam_dense(const float *__restrict__
 // (converted from bf16 bits in bf16 mode, where s is already bf16-rounded, so
 // s * W_label is exact in fp32).
 // ---------------------------------------------------------------------------
-template <bool BF16, int BM, int BN, int WM, int WN, int NBUF, bool STORE_H>
+template <int BM, int BN, int WM, int WN, int NBUF, bool STORE_H>
 __global__ __launch_bounds__(WM *WN * 64) void k_fwd_expand(
-    const typename Operand<BF16>::T *__restrict__ X, const typename Operand<BF16>::T *__restrict__ W,
-    const float *__restrict__ bias, LabelExpand ex, int M, int N, int K, float *__restrict__ H,
-    float *__restrict__ gpart) {
-  using T = typename Operand<BF16>::T;
+    const uint16_t *__restrict__ X, const uint16_t *__restrict__ W, const float *__restrict__ bias,
+    LabelExpand ex, int M, int N, int K, float *__restrict__ H, float *__restrict__ gpart) {
   constexpr int NT = WM * WN * 64;
   constexpr int TM = BM / WM, TN = BN / WN, MB = TM / 32, NB = TN / 32;
-  constexpr int kMain = nt_lds_elems<BF16, BM, BN, NBUF>() * (int)sizeof(T) / 4;  // in floats
+  constexpr int kMain = nt_lds_elems<true, BM, BN, NBUF>() / 2;  // in floats
   constexpr int kEpi = kMaxExpand * (WN * BM + BN);
   __shared__ __attribute__((aligned(16))) float smf[kMain > kEpi ? kMain : kEpi];
   const int nt = (N + BN - 1) / BN;
@@ -1103,7 +1656,8 @@ __global__ __launch_bounds__(WM *WN * 64) void k_fwd_expand(
   const int C = ex.n_classes;
 
   floatx16 acc[MB][NB];
-  nt_mainloop<BF16, BM, BN, WM, WN, NBUF>(X, W, M, N, K, m0, n0, reinterpret_cast<T *>(smf), acc);
+  nt_mainloop<true, BM, BN, WM, WN, NBUF>(X, W, M, N, K, m0, n0,
+                                          reinterpret_cast<uint16_t *>(smf), acc);
 
   // LDS after the main loop: gs [C][WN][BM] goodness partials, wl [BN][kMaxExpand]
   // the tile's label columns of W.
@@ -1112,10 +1666,7 @@ __global__ __launch_bounds__(WM *WN * 64) void k_fwd_expand(
   for (int i = tid; i < BN * C; i += NT) {
     const int j = i / C, c = i % C;
     const int col = min(n0 + j, N - 1);
-    if constexpr (BF16)
-      wl[j * kMaxExpand + c] = bf16_bits_to_f(W[(size_t)col * K + c]);
-    else
-      wl[j * kMaxExpand + c] = W[(size_t)col * K + c];
+    wl[j * kMaxExpand + c] = bf16_bits_to_f(W[(size_t)col * K + c]);
   }
   __syncthreads();
 
@@ -1175,6 +1726,41 @@ __global__ __launch_bounds__(WM *WN * 64) void k_fwd_expand(
 }
 
 // ---------------------------------------------------------------------------
+// Row factors of the fp32 weight gradient dW = sum_r (c_r h_r)^T x_hat_r.  The
+// split product wants both operands of row r under one power of two P that all
+// rows share.  With |c_r h| < 2^ea and |x_hat_r| < 2^eb the row's size is moved
+// half onto each side, c_r h / q and x_hat_r q with q = 2^((ea - eb) / 2), so
+// that a row whose product is 2^-n of the largest row's keeps its operands
+// within 2^(-n/2) of the f16 range's top: rows down to about 2^-20 of the
+// largest enter with all 24 bits.  m is the larger of the two exponents; P
+// comes from the largest m of all rows (dw_row_scale).
+// ---------------------------------------------------------------------------
+struct RowFactor {
+  float q;
+  int m;
+};
+__device__ __forceinline__ RowFactor row_factor(float abound, int eb) {
+  const int e = (int)(abs_bits(abound) >> 23);
+  RowFactor f;
+  if (e >= 255) {  // not finite: every sum must come out NaN
+    f.q = 1.f;
+    f.m = 255;
+    return f;
+  }
+  const int ea = max(e, 20) - 126;  // abound < 2^ea
+  const int t = (ea - eb) >> 1;
+  f.q = __uint_as_float((uint32_t)(127 + t) << 23);
+  f.m = max(ea - t, eb + t);
+  return f;
+}
+// Exponent bound of a row of x_hat: unit-norm rows, or rows with a row scale.
+__device__ __forceinline__ int input_exp(const float *xscale, int r) {
+  if (!xscale) return 1;
+  const int e = (int)(__float_as_uint(xscale[r]) >> 23);
+  return e >= 255 ? 1 : 15 - (e - 127);
+}
+
+// ---------------------------------------------------------------------------
 // Loss rows: g_r, c_r = 2 dL/dg_r, and per-block partial sums of the Eq. 1
 // terms (positives and negatives apart) over 64-row blocks, one wave per block;
 // the weight-gradient kernel finishes the scalar.  Each row's partials are
@@ -1190,9 +1776,13 @@ __global__ __launch_bounds__(kLossRows) void k_loss_rows(const float *__restrict
                                                           float *__restrict__ s_out,
                                                           float norm_eps,
                                                           const float *__restrict__ s_in,
-                                                          float *__restrict__ cs) {
+                                                          float *__restrict__ cs,
+                                                          const float *__restrict__ xscale,
+                                                          float *__restrict__ q,
+                                                          int32_t *__restrict__ mpart) {
   const int r = blockIdx.x * kLossRows + threadIdx.x;
   float lp = 0.f, ln = 0.f;
+  int em = -1000;
   if (r < R) {
     float gv = 0.f;
     int t = 0;
@@ -1218,12 +1808,20 @@ __global__ __launch_bounds__(kLossRows) void k_loss_rows(const float *__restrict
     }
     c[r] = cr;
     if (cs) cs[r] = cr * s_in[r];
+    if (q) {
+      const RowFactor f = row_factor(cr * sqrtf(gv), input_exp(xscale, r));
+      q[r] = f.q;
+      em = f.m;
+    }
   }
   lp = wave_sum(lp);
   ln = wave_sum(ln);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) em = max(em, __shfl_xor(em, o));
   if (threadIdx.x == 0) {
     lpart[2 * blockIdx.x] = lp;
     lpart[2 * blockIdx.x + 1] = ln;
+    if (mpart) mpart[blockIdx.x] = em;
   }
 }
 
@@ -1246,8 +1844,8 @@ template <int BM, int BN, int BK, int WM, int WN, int PF, bool BS>
 __global__ __launch_bounds__(WM *WN * 64) void k_dw_adam_f32(
     const float *__restrict__ Hm, const float *__restrict__ cvec, const float *__restrict__ Xh,
     const float *__restrict__ csvec, int M, int N, int K, float *__restrict__ W, float *__restrict__ mW, float *__restrict__ vW,
-    uint16_t *__restrict__ Wb, float *__restrict__ bvec, float *__restrict__ mbv,
-    float *__restrict__ vbv, AdamArgs ad, LossFinish lf) {
+    float *__restrict__ bvec, float *__restrict__ mbv, float *__restrict__ vbv, AdamArgs ad,
+    LossFinish lf) {
   constexpr int NT = WM * WN * 64;
   constexpr int TM = BM / WM, TN = BN / WN, MB = TM / 32, NB = TN / 32;
   constexpr int LDM = BM + 4, LDN = BN + 4;
@@ -1372,7 +1970,6 @@ __global__ __launch_bounds__(WM *WN * 64) void k_dw_adam_f32(
         W[idx] = p;
         mW[idx] = m;
         vW[idx] = v;
-        if (Wb) Wb[idx] = bf16_of(p);
       }
   }
 
@@ -1387,6 +1984,349 @@ __global__ __launch_bounds__(WM *WN * 64) void k_dw_adam_f32(
       float sum = 0.f;
 #pragma unroll
       for (int g2 = 0; g2 < KSA; ++g2) sum += red[g2 * BM + t];
+      float p = bvec[row], m = mbv[row], v = vbv[row];
+      adam_update(p, m, v, sum, ad);
+      bvec[row] = p;
+      mbv[row] = m;
+      vbv[row] = v;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// fp32 dW = (c.H)^T X_hat (+ db) with the Adam update fused, on the split
+// product.  M = d_out, N = d_in, K = R batch rows; both operands row-major over
+// K, so the LDS stages are [BK][BM] and [BK][BN], filled straight from global
+// memory.  A lane reads two consecutive columns of eight consecutive rows and
+// has the k-consecutive values of one column for each of two blocks, without a
+// transpose: MFMA row i of block mb is wave-tile column 2 i + mb (likewise N).
+// The row factors go into the split (split_pair takes one scale per value).
+// They are tabulated in LDS kDwRows rows at a time, already times P.
+// db sums c h of the same raw values in fp32, in the waves of column tile 0
+// with wn == 0.
+// Every wave ends with 16 / WK registers of each of its position's blocks and
+// runs Adam on them, two columns per access.
+// ---------------------------------------------------------------------------
+constexpr int kDwRows = 2048;
+
+// The 32 x 32 block (mb, nb) of a wave's tile on the fp32 matrix instructions:
+// rows mcol + 2 i + mb, columns ncol + 2 j + nb (clamped into the matrix).
+__device__ __forceinline__ void tn_exact(const float *__restrict__ Hm, const float *__restrict__ cv,
+                                         const float *__restrict__ sv, const float *__restrict__ Xh,
+                                         int M, int N, int K, int m, int n, int kg,
+                                         floatx16 &acc) {
+  const float *h = Hm + min(m, M - 1);
+  const float *x = Xh + min(n, N - 1);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll 1
+  for (int k0 = 0; k0 < K; k0 += 2) {
+    const int k = k0 + kg, kc = min(k, K - 1);
+    const float c = k < K ? (sv ? cv[kc] * sv[kc] : cv[kc]) : 0.f;
+    const float a = k < K ? h[(size_t)kc * M] * c : 0.f, b = k < K ? x[(size_t)kc * N] : 0.f;
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
+  }
+}
+
+// One chunk of kDwRows rows from row k0 on: acc += (fa h)^T (fb x), db += ct h
+// (DB), with the tables fa, fb, ct of the chunk's rows.
+template <class S, bool DB>
+__device__ __forceinline__ void tn_split_loop(const float *__restrict__ Hm,
+                                              const float *__restrict__ Xh, int M, int N, int K,
+                                              int k0, int m0, int n0, const Stages &st,
+                                              const float *fa, const float *fb, const float *ct,
+                                              floatx16 (&acc)[2][2], float2 &db) {
+  static_assert(S::MB == 2 && S::NB == 2, "64 x 64 wave tiles");
+  constexpr int BM = S::BM, BN = S::BN, BK = S::BK, NBUF = S::NBUF;
+  constexpr int IA = BM * BK / 256 / S::NW, IB = BN * BK / 256 / S::NW;
+  static_assert(IA * S::NW * 256 == BM * BK && IB * S::NW * 256 == BN * BK, "wave loads");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave % S::WK, wm = wave / S::WK / S::WN, wn = wave / S::WK % S::WN;
+  const int li = lane & 31, kg = lane >> 5;
+  const int kend = min(K, k0 + kDwRows), nk = (kend - k0 + BK - 1) / BK;
+  auto issue = [&](int kt, int buf) {
+    float *St = st.p[buf];
+    // in scalar registers: the descriptors must be uniform to the compiler too
+    const int k = __builtin_amdgcn_readfirstlane(k0 + kt * BK);
+    const int rows = max(0, min(BK, kend - k));
+    const int kb = min(k, K - 1);  // keeps the base inside the matrix when no row is left
+    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(
+        Hm + (size_t)kb * M + m0, rows ? (uint32_t)((rows * M - m0) * 4) : 0u);
+    const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(
+        Xh + (size_t)kb * N + n0, rows ? (uint32_t)((rows * N - n0) * 4) : 0u);
+#pragma unroll
+    for (int i = 0; i < IA; ++i) {
+      const int f = (wave * IA + i) * 256 + lane * 4;
+      const uint32_t o = (uint32_t)((f / BM * M + f % BM) * 4);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void *)(St + (wave * IA + i) * 256), 16, o,
+                                               0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < IB; ++i) {
+      const int f = (wave * IB + i) * 256 + lane * 4;
+      const uint32_t o = (uint32_t)((f / BN * N + f % BN) * 4);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rb, (lds_void *)(St + BM * BK + (wave * IB + i) * 256), 16, o, 0, 0, 0);
+    }
+  };
+  struct Frags {
+    HalfPair a[2], b[2];
+  } f[2];
+  const int kr = wk * 16 + kg * 8;  // the lane's first row of a stage
+  auto load_split = [&](int kt, int buf, Frags &n) {
+    const float *As = st.p[buf] + kr * BM + wm * 64 + 2 * li;
+    const float *Bs = st.p[buf] + BM * BK + kr * BN + wn * 64 + 2 * li;
+    float2_t ar[8], br[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) ar[j] = *reinterpret_cast<const float2_t *>(As + j * BM);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) br[j] = *reinterpret_cast<const float2_t *>(Bs + j * BN);
+    float pa[8], pb[8];
+    const int t = kt * BK + kr;
+#pragma unroll
+    for (int j = 0; j < 8; j += 4) {
+      const float4_t va = *reinterpret_cast<const float4_t *>(fa + t + j);
+      const float4_t vb = *reinterpret_cast<const float4_t *>(fb + t + j);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        pa[j + i] = va[i];
+        pb[j + i] = vb[i];
+      }
+    }
+    if constexpr (DB) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float c = ct[t + j];
+        db.x += c * ar[j][0];
+        db.y += c * ar[j][1];
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      split_pair(ar[0][b], pa[0], ar[1][b], pa[1], n.a[b].h.x, n.a[b].l.x);
+      split_pair(ar[2][b], pa[2], ar[3][b], pa[3], n.a[b].h.y, n.a[b].l.y);
+      split_pair(ar[4][b], pa[4], ar[5][b], pa[5], n.a[b].h.z, n.a[b].l.z);
+      split_pair(ar[6][b], pa[6], ar[7][b], pa[7], n.a[b].h.w, n.a[b].l.w);
+      split_pair(br[0][b], pb[0], br[1][b], pb[1], n.b[b].h.x, n.b[b].l.x);
+      split_pair(br[2][b], pb[2], br[3][b], pb[3], n.b[b].h.y, n.b[b].l.y);
+      split_pair(br[4][b], pb[4], br[5][b], pb[5], n.b[b].h.z, n.b[b].l.z);
+      split_pair(br[6][b], pb[6], br[7][b], pb[7], n.b[b].h.w, n.b[b].l.w);
+    }
+  };
+  auto products = [&](Frags &c) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = mfma_f16(c.a[i >> 1].l, c.b[i & 1].h, acc[i >> 1][i & 1]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = mfma_f16(c.a[i >> 1].h, c.b[i & 1].l, acc[i >> 1][i & 1]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = mfma_f16(c.a[i >> 1].h, c.b[i & 1].h, acc[i >> 1][i & 1]);
+  };
+#pragma unroll
+  for (int j = 0; j < NBUF; ++j) issue(j, j);
+  __builtin_amdgcn_s_waitcnt(vmcnt_wait((NBUF - 1) * (IA + IB)));
+  lds_barrier();
+  load_split(0, 0, f[0]);
+  // Stage kt's products run while stage kt + 1 is read from LDS and split; the
+  // barrier says that stage kt + 1 has landed and every wave is done with
+  // stage kt's LDS, which stage kt + NBUF then refills.
+  auto step = [&](int kt, int buf, int nxt, Frags &c, Frags &n) {
+    __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0((NBUF - 2) * (IA + IB)));
+    lds_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    issue(kt + NBUF, buf);
+    __builtin_amdgcn_sched_barrier(0);
+    products(c);
+    load_split(kt + 1, nxt, n);  // past the end: rows and factors of zeros
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  constexpr int U = NBUF % 2 == 0 ? NBUF : 2 * NBUF;
+  int kt = 0;
+  for (; kt + U <= nk; kt += U)
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+      step(kt + j, j % NBUF, (j + 1) % NBUF, f[j & 1], f[(j + 1) & 1]);
+#pragma unroll
+  for (int j = 0; j < U - 1; ++j)
+    if (kt + j < nk) step(kt + j, j % NBUF, (j + 1) % NBUF, f[j & 1], f[(j + 1) & 1]);
+  __builtin_amdgcn_s_waitcnt(vmcnt_wait(0));
+  lds_barrier();
+}
+
+template <class S>
+__global__ __launch_bounds__(S::threads, S::NW == 4 && S::WK == 4 ? 1 : 2) void k_dw_adam_split(
+    const float *__restrict__ Hm, const float *__restrict__ Xh, DwRows rows, int M, int N, int K,
+    float *__restrict__ W, float *__restrict__ mW, float *__restrict__ vW,
+    float *__restrict__ bvec, float *__restrict__ mbv, float *__restrict__ vbv, AdamArgs ad,
+    LossFinish lf) {
+  constexpr int RPW = 16 / S::WK;  // registers of each block that a wave finishes
+  FF_SPLIT_STAGES(S, st);
+  // one stage past the chunk: the pipeline reads factors one stage ahead
+  constexpr int kTab = kDwRows + S::BK;
+  __shared__ __attribute__((aligned(16))) float fa[kTab], fb[kTab], ct[kTab];
+  __shared__ int emax[S::NW];
+  const int nt = (N + S::BN - 1) / S::BN;
+  int tm, tn;
+  tile_of(blockIdx.x, (M + S::BM - 1) / S::BM, nt, tm, tn);
+  const int m0 = __builtin_amdgcn_readfirstlane(tm * S::BM);
+  const int n0 = __builtin_amdgcn_readfirstlane(tn * S::BN);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave % S::WK, wmn = wave / S::WK, wm = wmn / S::WN, wn = wmn % S::WN;
+  const int li = lane & 31, kg = lane >> 5;
+
+  if (lf.loss && blockIdx.x == 0 && tid == 0) {
+    float sp = 0.f, sn = 0.f;
+    for (int i = 0; i < lf.nblk; ++i) {
+      sp += lf.lpart[2 * i];
+      sn += lf.lpart[2 * i + 1];
+    }
+    lf.loss[0] = sp / (float)lf.n_pos + sn / (float)lf.n_neg;
+  }
+
+  // P = 2^(15 - the largest row exponent); NaN when a row is not finite
+  int em = -1000;
+  for (int i = tid; i < rows.nm; i += S::threads) em = max(em, rows.m[i]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) em = max(em, __shfl_xor(em, o));
+  if (lane == 0) emax[wave] = em;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < S::NW; ++w) em = max(em, emax[w]);
+  const float P = __uint_as_float(em >= 255 ? 0x7fc00000u : (uint32_t)(127 + 15 - em) << 23);
+
+  floatx16 acc[2][2];
+#pragma unroll
+  for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.f;
+  float2 db = make_float2(0.f, 0.f);
+  const bool do_db = tn == 0 && wn == 0;  // uniform per wave
+#pragma unroll 1
+  for (int k0 = 0; k0 < K; k0 += kDwRows) {
+    if (k0) __syncthreads();
+    for (int i = tid; i < kTab; i += S::threads) {
+      const int k = k0 + i;
+      const bool ok = k < K && i < kDwRows;
+      const float c = ok ? rows.c[k] : 0.f, q = ok ? rows.q[k] : 1.f;
+      fa[i] = ok ? c * pow2_inv(q) * P : 0.f;
+      fb[i] = ok ? (rows.s ? rows.s[k] : 1.f) * q * P : 0.f;
+      ct[i] = c;
+    }
+    __syncthreads();
+    if (do_db)
+      tn_split_loop<S, true>(Hm, Xh, M, N, K, k0, m0, n0, st, fa, fb, ct, acc, db);
+    else
+      tn_split_loop<S, false>(Hm, Xh, M, N, K, k0, m0, n0, st, fa, fb, ct, acc, db);
+  }
+
+  // k-split reduction: wave wk finishes registers wk * RPW .. of every block,
+  // NBR of the four blocks at a time
+  float own[2][2][RPW];
+  constexpr int NBR = S::NW * (S::WK - 1) * RPW * 256 <= S::STAGE ? 4 : 2;
+  static_assert(S::NW * (S::WK - 1) * RPW * 64 * NBR <= S::STAGE, "LDS");
+  float *base = sm0 + wmn * S::WK * (S::WK - 1) * RPW * 64 * NBR;
+#pragma unroll
+  for (int b0 = 0; b0 < 4; b0 += NBR) {
+    if (b0) __syncthreads();
+#pragma unroll
+    for (int o = 0; o < S::WK; ++o) {
+      float *dst = base + (o * (S::WK - 1) + (wk < o ? wk : wk - 1)) * RPW * 64 * NBR + lane;
+#pragma unroll
+      for (int b = b0; b < b0 + NBR; ++b)
+#pragma unroll
+        for (int j = 0; j < RPW; ++j) {
+          const float v = acc[b >> 1][b & 1][o * RPW + j];
+          if (wk == o)
+            own[b >> 1][b & 1][j] = v;
+          else
+            dst[((b - b0) * RPW + j) * 64] = v;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < S::WK - 1; ++g) {
+      const float *src = base + (wk * (S::WK - 1) + g) * RPW * 64 * NBR + lane;
+#pragma unroll
+      for (int b = b0; b < b0 + NBR; ++b)
+#pragma unroll
+        for (int j = 0; j < RPW; ++j) own[b >> 1][b & 1][j] += src[((b - b0) * RPW + j) * 64];
+    }
+  }
+  const float up = pow2_inv(P);
+  const int col = n0 + wn * 64 + 2 * li;  // N is even: both columns are in or both out
+  // Past M or N a tile row of LDS runs on into the next batch row, whose own
+  // factor may be another: those sums are never stored, whatever they are.
+  int bad = 0;
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int j = 0; j < RPW; ++j) {
+      float &v = own[b >> 1][b & 1][j];
+      const int row = m0 + wm * 64 + 2 * acc_row(wk * RPW + j, kg) + (b >> 1);
+      bad |= row < M && col < N && v != v;
+      v = v * up * up;
+    }
+  if (__syncthreads_or(bad)) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      floatx16 e;
+      tn_exact(Hm, rows.c, rows.s, Xh, M, N, K, m0 + wm * 64 + 2 * li + (b >> 1),
+               n0 + wn * 64 + 2 * li + (b & 1), kg, e);
+#pragma unroll
+      for (int o = 0; o < S::WK; ++o)
+        if (wk == o)
+#pragma unroll
+          for (int j = 0; j < RPW; ++j) own[b >> 1][b & 1][j] = e[o * RPW + j];
+    }
+  }
+
+  // Adam on the wave's elements, two columns per access, eight rows in flight.
+#pragma unroll
+  for (int g = 0; g < 2 * RPW / 8; ++g) {
+    float2 p[8], m[8], v[8];
+    size_t o[8];
+    bool ok[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int e = g * 8 + u, mb = e / RPW, j = e % RPW;
+      const int row = m0 + wm * 64 + 2 * acc_row(wk * RPW + j, kg) + mb;
+      ok[u] = row < M && col < N;
+      o[u] = ok[u] ? (size_t)row * N + col : 0;
+      if (ok[u]) {
+        p[u] = *reinterpret_cast<const float2 *>(W + o[u]);
+        m[u] = *reinterpret_cast<const float2 *>(mW + o[u]);
+        v[u] = *reinterpret_cast<const float2 *>(vW + o[u]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (!ok[u]) continue;
+      const int e = g * 8 + u, mb = e / RPW, j = e % RPW;
+      adam_update(p[u].x, m[u].x, v[u].x, own[mb][0][j], ad);
+      adam_update(p[u].y, m[u].y, v[u].y, own[mb][1][j], ad);
+      *reinterpret_cast<float2 *>(W + o[u]) = p[u];
+      *reinterpret_cast<float2 *>(mW + o[u]) = m[u];
+      *reinterpret_cast<float2 *>(vW + o[u]) = v[u];
+    }
+  }
+
+  // db: the waves wn == 0 of each column position, their half-waves and k-split
+  // partners in fixed order, then Adam on b (column-tile 0 only).
+  if (tn == 0) {
+    float *red = sm0;  // [WK][2][BM]
+    __syncthreads();
+    if (wn == 0)
+      *reinterpret_cast<float2 *>(red + (wk * 2 + kg) * S::BM + wm * 64 + 2 * li) = db;
+    __syncthreads();
+    for (int t = tid; t < S::BM; t += S::threads) {
+      const int row = m0 + t;
+      if (row >= M) continue;
+      float sum = 0.f;
+#pragma unroll
+      for (int g = 0; g < 2 * S::WK; ++g) sum += red[g * S::BM + t];
       float p = bvec[row], m = mbv[row], v = vbv[row];
       adam_update(p, m, v, sum, ad);
       bvec[row] = p;
@@ -2009,18 +2949,12 @@ __global__ __launch_bounds__(kBlock) void k_head_logits(HeadFeatures hf, int n, 
   }
 }
 
-// Backprop of a layer's classifier into the layer: one thread per 4
-// consecutive units of a row.
-template <int CC>  // class-count bound, as in k_head_logits
-__global__ __launch_bounds__(kBlock) void k_po_dz(const float *__restrict__ H,
-                                                  const float *__restrict__ G,
-                                                  const float *__restrict__ Wc, int R, int D,
-                                                  int C, float *__restrict__ dZ,
-                                                  float *__restrict__ ones) {
-  const int q = blockIdx.x * kBlock + threadIdx.x;
-  const int d4 = D >> 2;
-  if (q >= R * d4) return;
-  const int r = q / d4, j = 4 * (q % d4);
+// dZ of four consecutive units j.. of row r: sum over classes of G[r][c] Wc[c][j],
+// through the ReLU's derivative (h = 0 wherever z <= 0).
+template <int CC>
+__device__ __forceinline__ float4 po_dz4(const float *__restrict__ H, const float *__restrict__ G,
+                                         const float *__restrict__ Wc, int r, int j, int D,
+                                         int C) {
   const float4 h = ld4(H + (size_t)r * D + j);
   float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
@@ -2034,12 +2968,68 @@ __global__ __launch_bounds__(kBlock) void k_po_dz(const float *__restrict__ H,
     g.z += gc * w.z;
     g.w += gc * w.w;
   }
-  g.x = h.x > 0.f ? g.x : 0.f;  // the ReLU derivative (h = 0 wherever z <= 0)
+  g.x = h.x > 0.f ? g.x : 0.f;
   g.y = h.y > 0.f ? g.y : 0.f;
   g.z = h.z > 0.f ? g.z : 0.f;
   g.w = h.w > 0.f ? g.w : 0.f;
-  st4(dZ + (size_t)r * D + j, g);
+  return g;
+}
+
+// Backprop of a layer's classifier into the layer: one thread per 4
+// consecutive units of a row.
+template <int CC>  // class-count bound, as in k_head_logits
+__global__ __launch_bounds__(kBlock) void k_po_dz(const float *__restrict__ H,
+                                                  const float *__restrict__ G,
+                                                  const float *__restrict__ Wc, int R, int D,
+                                                  int C, float *__restrict__ dZ,
+                                                  float *__restrict__ ones) {
+  const int q = blockIdx.x * kBlock + threadIdx.x;
+  const int d4 = D >> 2;
+  if (q >= R * d4) return;
+  const int r = q / d4, j = 4 * (q % d4);
+  st4(dZ + (size_t)r * D + j, po_dz4<CC>(H, G, Wc, r, j, D, C));
   if (j == 0) ones[r] = 1.f;
+}
+
+// The same with one wave per row, which then also has the row's largest |dZ|:
+// the row factors of the fp32 weight gradient (q, and the largest exponent of
+// the workgroup's four rows in mpart).
+template <int CC>
+__global__ __launch_bounds__(kBlock) void k_po_dz_rows(const float *__restrict__ H,
+                                                       const float *__restrict__ G,
+                                                       const float *__restrict__ Wc, int R, int D,
+                                                       int C, float *__restrict__ dZ,
+                                                       float *__restrict__ ones,
+                                                       const float *__restrict__ xscale,
+                                                       float *__restrict__ q,
+                                                       int32_t *__restrict__ mpart) {
+  __shared__ int em[kBlock / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = blockIdx.x * (kBlock / 64) + wave;
+  if (lane == 0) em[wave] = -1000;
+  if (r < R) {  // uniform per wave
+    uint32_t m = 0;
+    for (int j = 4 * lane; j < D; j += 256) {
+      const float4 g = po_dz4<CC>(H, G, Wc, r, j, D, C);
+      st4(dZ + (size_t)r * D + j, g);
+      m = max(max(m, max(abs_bits(g.x), abs_bits(g.y))), max(abs_bits(g.z), abs_bits(g.w)));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+    if (lane == 0) {
+      const RowFactor f = row_factor(__uint_as_float(m), input_exp(xscale, r));
+      ones[r] = 1.f;
+      q[r] = f.q;
+      em[wave] = f.m;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int e = em[0];
+#pragma unroll
+    for (int w = 1; w < kBlock / 64; ++w) e = max(e, em[w]);
+    mpart[blockIdx.x] = e;
+  }
 }
 
 // Classifier weight-gradient partials.  A workgroup covers 64 consecutive
@@ -2177,8 +3167,16 @@ __global__ __launch_bounds__(kBlock) void k_goodness(const float *__restrict__ g
                                                      float *__restrict__ s_out, float norm_eps) {
   const int r = blockIdx.x * kBlock + threadIdx.x;
   if (r >= R) return;
-  float gv = 0.f;
-  for (int t = 0; t < nt; ++t) gv += gpart[(size_t)t * R + r];
+  float gv = 0.f;  // in tile order, eight loads in flight
+  int t = 0;
+  for (; t + 8 <= nt; t += 8) {
+    float p[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p[j] = gpart[(size_t)(t + j) * R + r];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) gv += p[j];
+  }
+  for (; t < nt; ++t) gv += gpart[(size_t)t * R + r];
   if (g) g[r] = gv;
   if (s_out) s_out[r] = 1.f / (sqrtf(gv) + norm_eps);
   if (out) out[r] = accumulate ? out[r] + gv : gv;
@@ -2266,7 +3264,7 @@ using DwSmallBf16 = Tile<64, 64, 64, 2, 2, 2>;
 template <bool BF16>
 struct FwdTiles;
 template <>
-struct FwdTiles<false> {
+struct FwdTiles<false> {  // the fp32 instructions (training epochs)
   using Huge = Tile<128, 256, 32, 2, 4, 2>;
   using Large = Tile<128, 128, 32, 4, 4, 2>;
   using Big = Large;
@@ -2281,6 +3279,16 @@ struct FwdTiles<true> {
   using Full = Tile<128, 128, 64, 4, 2, 3>;
   using Small = Tile<64, 64, 64, 2, 2, 3>;
 };
+// fp32 split-product tiles, all but the smallest on eight waves of 64x64 or
+// (Huge) 128x64: forward with two or three LDS stages, weight gradient with two
+// and four or eight waves.
+using SplitHuge = SplitTile<256, 128, 2, 2, 2>;
+using SplitBig = SplitTile<128, 128, 2, 2, 2, 3>;
+using SplitMid = SplitTile<128, 64, 2, 1, 4, 3>;
+using SplitSmall = SplitTile<64, 64, 1, 1, 4>;
+using SplitDwPair = SplitTile<128, 64, 2, 1, 2>;  // four waves, two workgroups per CU
+using SplitDwMid = SplitTile<128, 64, 2, 1, 4>;   // eight waves, one workgroup per CU
+using SplitDwSmall = SplitTile<64, 64, 1, 1, 4>;
 template <class T>
 struct TileTag {
   using type = T;
@@ -2298,34 +3306,63 @@ void fwd_tile(int M, int N, F &&f) {
   if (L::Full::tiles(M, N) >= kCUs) return f(TileTag<typename L::Full>{});
   f(TileTag<typename L::Small>{});
 }
-
-// The fp32 large tile also takes grids of at least three quarters of the CUs:
-// layer 0's 2000x784 weights (224 tiles) ran 91 us on it over 2048 rows,
-// 98 us on 416 small tiles.
-inline bool dw_big(int M, int N, int dtype) {
-  return dtype ? DwBigBf16::tiles(M, N) >= kCUs : 4 * DwBig::tiles(M, N) >= 3 * kCUs;
+// The split product's forward tile: the one with the least rounds x time per
+// round.  A round puts one tile on every CU, and the times per round are those
+// measured at K = 2000 (us): 256x128 83, 128x128 60 (53 on half the CUs, 66 on
+// all of them, where the power limit lowers the clock), 128x64 38, 64x64 22.
+// So, measured, 1024x2000x2000 takes 128x64 (38 us; 64x64 40, 128x128 52),
+// 2048x2000x2000 128x128 (66 us; 128x64 75, 64x64 81, 256x128 83), 1216x2000x784
+// 128x128 (26 us; 64x64 28, 128x64 34), 997x756x1236 64x64 (16 us; 128x64 22),
+// 20480x2000x2000 256x128 (580 us; 128x128 665, 128x64 770, 64x64 790).
+template <bool LARGE = true, class F>
+void fwd_tile_split(int M, int N, F &&f) {
+  auto cost = [&](auto t, long us) {
+    return (decltype(t)::type::tiles(M, N) + kCUs - 1) / kCUs * us;
+  };
+  const long small = cost(TileTag<SplitSmall>{}, 22), mid = cost(TileTag<SplitMid>{}, 38),
+             big = cost(TileTag<SplitBig>{}, 60);
+  if constexpr (LARGE) {
+    const long huge = cost(TileTag<SplitHuge>{}, 83);
+    if (huge < big && huge < mid && huge < small) return f(TileTag<SplitHuge>{});
+  }
+  if (big <= mid && big <= small) return f(TileTag<SplitBig>{});
+  if (mid <= small) return f(TileTag<SplitMid>{});
+  f(TileTag<SplitSmall>{});
 }
 
-int fwd_col_tiles(int rows, int n_cols, int dtype) {
+// The split weight gradient's tile.  64x64 while its grid leaves no CU with a
+// second tile (500x784 over 1024 rows: 21 us, 128x64 26), then 128x64 on eight
+// waves as long as that holds for it (2000x784 over 1216 rows: 32 us; on four
+// waves 40, 64x64 47, 128x128 58), then 128x64 on four waves, two workgroups per
+// CU: one's Adam traffic runs beside the other's products (2000x2000 over 2048
+// rows: 77 us; on eight waves 87, 128x128 91-94, 64x64 138).
+template <class F>
+void dw_tile_split(int M, int N, F &&f) {
+  if (SplitDwSmall::tiles(M, N) <= kCUs) return f(TileTag<SplitDwSmall>{});
+  if (SplitDwMid::tiles(M, N) <= kCUs) return f(TileTag<SplitDwMid>{});
+  f(TileTag<SplitDwPair>{});
+}
+
+int fwd_col_tiles(int rows, int n_cols, int dtype, bool split) {
   int bn = 0;
-  auto pick = [&](auto t) { bn = decltype(t)::type::bn; };
   if (dtype)
-    fwd_tile<true>(rows, n_cols, pick);
+    fwd_tile<true>(rows, n_cols, [&](auto t) { bn = decltype(t)::type::bn; });
+  else if (!split)
+    fwd_tile<false>(rows, n_cols, [&](auto t) { bn = decltype(t)::type::bn; });
   else
-    fwd_tile<false>(rows, n_cols, pick);
+    fwd_tile_split(rows, n_cols, [&](auto t) { bn = decltype(t)::type::BN; });
   return (int)cdiv(n_cols, bn);
 }
 int fwd_expand_col_tiles(int rows, int n_cols, int dtype) {
   int bn = 0;
-  auto pick = [&](auto t) { bn = decltype(t)::type::bn; };
   if (dtype)
-    fwd_tile<true, false>(rows, n_cols, pick);
+    fwd_tile<true, false>(rows, n_cols, [&](auto t) { bn = decltype(t)::type::bn; });
   else
-    fwd_tile<false, false>(rows, n_cols, pick);
+    fwd_tile_split<false>(rows, n_cols, [&](auto t) { bn = decltype(t)::type::BN; });
   return (int)cdiv(n_cols, bn);
 }
 int fwd_col_tiles_max(int n_cols) {
-  return (int)cdiv(n_cols, std::min(FwdTiles<false>::Small::bn, FwdTiles<true>::Small::bn));
+  return (int)cdiv(n_cols, std::min({(int)SplitSmall::BN, (int)FwdTiles<false>::Small::bn, (int)FwdTiles<true>::Small::bn}));
 }
 
 int loss_blocks(int rows) { return (int)cdiv(rows, kLossRows); }
@@ -2334,124 +3371,166 @@ int padded_rows(int rows) { return (int)cdiv(rows, kTRows) * kTRows; }
 
 template <int NV>
 void embed_norm_reg(const RowMap &m, int rows, int d, float eps, bool normalise, bool bf16_out,
-                    void *out, float *scale_out, hipStream_t s) {
-  const dim3 grid(cdiv(rows, kBlock / 64));
+                    void *out, float *scale_out, const RowScaleJob &job, hipStream_t s) {
+  const dim3 grid(cdiv(rows, kBlock / 64) + cdiv(job.n, kBlock / 64));
   if (bf16_out)
     hipLaunchKernelGGL((k_embed_norm_reg<NV, true>), grid, dim3(kBlock), 0, s, m, rows, d, eps,
-                       (int)normalise, out, scale_out);
+                       (int)normalise, out, scale_out, job);
   else
     hipLaunchKernelGGL((k_embed_norm_reg<NV, false>), grid, dim3(kBlock), 0, s, m, rows, d, eps,
-                       (int)normalise, out, scale_out);
+                       (int)normalise, out, scale_out, job);
 }
 
 hipError_t launch_embed_norm(const RowMap &m, int rows, int d, float eps, bool normalise,
-                             bool bf16_out, void *out, float *scale_out, hipStream_t s) {
+                             bool bf16_out, void *out, float *scale_out, hipStream_t s,
+                             const RowScaleJob *scales) {
   if (rows <= 0) return hipSuccess;
+  if (scales && bf16_out) return hipErrorInvalidValue;
+  const RowScaleJob job = scales ? *scales : RowScaleJob{nullptr, nullptr, 0, 0};
   const int nv = (int)cdiv(d / 4, 64);  // float4 per lane for the whole row
   if (nv <= 1) {
-    embed_norm_reg<1>(m, rows, d, eps, normalise, bf16_out, out, scale_out, s);
+    embed_norm_reg<1>(m, rows, d, eps, normalise, bf16_out, out, scale_out, job, s);
   } else if (nv <= 2) {
-    embed_norm_reg<2>(m, rows, d, eps, normalise, bf16_out, out, scale_out, s);
+    embed_norm_reg<2>(m, rows, d, eps, normalise, bf16_out, out, scale_out, job, s);
   } else if (nv <= 4) {
-    embed_norm_reg<4>(m, rows, d, eps, normalise, bf16_out, out, scale_out, s);
+    embed_norm_reg<4>(m, rows, d, eps, normalise, bf16_out, out, scale_out, job, s);
   } else if (nv <= 8) {
-    embed_norm_reg<8>(m, rows, d, eps, normalise, bf16_out, out, scale_out, s);
+    embed_norm_reg<8>(m, rows, d, eps, normalise, bf16_out, out, scale_out, job, s);
   } else if (nv <= 12) {
-    embed_norm_reg<12>(m, rows, d, eps, normalise, bf16_out, out, scale_out, s);
+    embed_norm_reg<12>(m, rows, d, eps, normalise, bf16_out, out, scale_out, job, s);
   } else if (nv <= 16) {
-    embed_norm_reg<16>(m, rows, d, eps, normalise, bf16_out, out, scale_out, s);
+    embed_norm_reg<16>(m, rows, d, eps, normalise, bf16_out, out, scale_out, job, s);
   } else {
-    const dim3 grid(cdiv(rows, kBlock / 64));
+    const dim3 grid(cdiv(rows, kBlock / 64) + cdiv(job.n, kBlock / 64));
     if (bf16_out)
       hipLaunchKernelGGL(k_embed_norm<true>, grid, dim3(kBlock), 0, s, m, rows, d, eps,
-                         (int)normalise, out, scale_out);
+                         (int)normalise, out, scale_out, job);
     else
       hipLaunchKernelGGL(k_embed_norm<false>, grid, dim3(kBlock), 0, s, m, rows, d, eps,
-                         (int)normalise, out, scale_out);
+                         (int)normalise, out, scale_out, job);
   }
   return hipGetLastError();
 }
 
+hipError_t launch_row_scales(const RowScaleJob *jobs, int count, hipStream_t s) {
+  if (count < 1 || count > kMaxScaleJobs) return hipErrorInvalidValue;
+  RowScaleJobs a{};
+  a.count = count;
+  unsigned blocks = 0;
+  for (int j = 0; j < count; ++j) {
+    if (jobs[j].n <= 0 || jobs[j].d <= 0 || jobs[j].d % 4) return hipErrorInvalidValue;
+    a.job[j] = jobs[j];
+    blocks += cdiv(jobs[j].n, kBlock / 64);
+  }
+  hipLaunchKernelGGL(k_row_scales, dim3(blocks), dim3(kBlock), 0, s, a);
+  return hipGetLastError();
+}
+
 template <bool BF16, class T>
-void fwd_launch(const void *x, const void *w, const float *bias, const float *rowscale, int M,
-                int N, int K, float *H, float *gpart, hipStream_t s) {
-  using E = typename Operand<BF16>::T;
+void fwd_launch(const typename Operand<BF16>::T *x, const typename Operand<BF16>::T *w,
+                const float *bias, const float *rowscale, int M, int N, int K, float *H,
+                float *gpart, hipStream_t s) {
   const dim3 grid(T::tiles(M, N));
-  const E *xe = static_cast<const E *>(x);
-  const E *we = static_cast<const E *>(w);
   static_assert(T::bk == nt_bk<BF16>(), "forward k-tile is 128 bytes");
   if constexpr (BF16 && T::four) {
     static_assert(T::wm == 2 && T::wn == 2, "four-wave tile");
     if (H)
-      hipLaunchKernelGGL((k_fwd4<T::bm, T::bn, T::pf, true>), grid, dim3(256), 0, s, xe, we, bias,
-                         rowscale, M, N, K, H, gpart);
+      hipLaunchKernelGGL((k_fwd4<T::bm, T::bn, T::pf, true>), grid, dim3(256), 0, s, x, w, bias, M,
+                         N, K, H, gpart);
     else
-      hipLaunchKernelGGL((k_fwd4<T::bm, T::bn, T::pf, false>), grid, dim3(256), 0, s, xe, we,
-                         bias, rowscale, M, N, K, H, gpart);
+      hipLaunchKernelGGL((k_fwd4<T::bm, T::bn, T::pf, false>), grid, dim3(256), 0, s, x, w, bias,
+                         M, N, K, H, gpart);
   } else if (H) {
     hipLaunchKernelGGL((k_fwd<BF16, T::bm, T::bn, T::wm, T::wn, T::pf, true>), grid,
-                       dim3(T::threads), 0, s, xe, we, bias, rowscale, M, N, K, H, gpart);
+                       dim3(T::threads), 0, s, x, w, bias, rowscale, M, N, K, H, gpart);
   } else {
     hipLaunchKernelGGL((k_fwd<BF16, T::bm, T::bn, T::wm, T::wn, T::pf, false>), grid,
-                       dim3(T::threads), 0, s, xe, we, bias, rowscale, M, N, K, H, gpart);
+                       dim3(T::threads), 0, s, x, w, bias, rowscale, M, N, K, H, gpart);
   }
 }
 
-hipError_t launch_fwd(int dtype, const void *X, const void *W, const float *bias,
-                      const float *rowscale, int M, int N, int K, float *H, float *gpart,
-                      hipStream_t s) {
+template <class S>
+void fwd_launch_split(const float *x, const float *w, const float *bias, const float *rowscale,
+                    const float *xscale, const float *wscale, int M, int N, int K, float *H,
+                    float *gpart, hipStream_t s) {
+  const dim3 grid(S::tiles(M, N));
+  if (H)
+    hipLaunchKernelGGL((k_fwd_split<S, true>), grid, dim3(S::threads), 0, s, x, w, bias, rowscale,
+                       xscale, wscale, M, N, K, H, gpart);
+  else
+    hipLaunchKernelGGL((k_fwd_split<S, false>), grid, dim3(S::threads), 0, s, x, w, bias, rowscale,
+                       xscale, wscale, M, N, K, H, gpart);
+}
+
+hipError_t launch_fwd_bf16(const uint16_t *X, const uint16_t *W, const float *bias, int M, int N,
+                           int K, float *H, float *gpart, hipStream_t s) {
   if (M <= 0) return hipSuccess;
   if (K > kMaxWidth) return hipErrorInvalidValue;
-  if (dtype == 0)
-    fwd_tile<false>(M, N, [&](auto t) {
-      fwd_launch<false, typename decltype(t)::type>(X, W, bias, rowscale, M, N, K, H, gpart, s);
+  fwd_tile<true>(M, N, [&](auto t) {
+    fwd_launch<true, typename decltype(t)::type>(X, W, bias, nullptr, M, N, K, H, gpart, s);
+  });
+  return hipGetLastError();
+}
+
+hipError_t launch_fwd_f32(const float *X, const float *W, const float *bias, const float *rowscale,
+                          const float *xscale, const float *wscale, int M, int N, int K, float *H,
+                          float *gpart, hipStream_t s) {
+  if (M <= 0) return hipSuccess;
+  if (K > kMaxWidth || (xscale && (rowscale || !wscale))) return hipErrorInvalidValue;
+  if (wscale)
+    fwd_tile_split(M, N, [&](auto t) {
+      fwd_launch_split<typename decltype(t)::type>(X, W, bias, rowscale, xscale, wscale, M, N, K,
+                                                   H, gpart, s);
     });
   else
-    fwd_tile<true>(M, N, [&](auto t) {
-      fwd_launch<true, typename decltype(t)::type>(X, W, bias, rowscale, M, N, K, H, gpart, s);
+    fwd_tile<false>(M, N, [&](auto t) {
+      fwd_launch<false, typename decltype(t)::type>(X, W, bias, rowscale, M, N, K, H, gpart, s);
     });
   return hipGetLastError();
 }
 
-template <bool BF16, class T>
-void fwd_expand_launch(const void *x, const void *w, const float *bias, const LabelExpand &ex,
-                       int M, int N, int K, float *H, float *gpart, hipStream_t s) {
-  using E = typename Operand<BF16>::T;
-  const dim3 grid(T::tiles(M, N));
-  const E *xe = static_cast<const E *>(x);
-  const E *we = static_cast<const E *>(w);
-  static_assert(T::bk == nt_bk<BF16>(), "forward k-tile is 128 bytes");
-  if (H)
-    hipLaunchKernelGGL((k_fwd_expand<BF16, T::bm, T::bn, T::wm, T::wn, T::pf, true>), grid,
-                       dim3(T::threads), 0, s, xe, we, bias, ex, M, N, K, H, gpart);
-  else
-    hipLaunchKernelGGL((k_fwd_expand<BF16, T::bm, T::bn, T::wm, T::wn, T::pf, false>), grid,
-                       dim3(T::threads), 0, s, xe, we, bias, ex, M, N, K, H, gpart);
-}
-
 hipError_t launch_fwd_expand(int dtype, const void *X, const void *W, const float *bias,
-                             const LabelExpand &ex, int M, int N, int K, float *H, float *gpart,
-                             hipStream_t s) {
+                             const LabelExpand &ex, const float *wscale, int M, int N, int K,
+                             float *H, float *gpart, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  if (ex.n_classes < 1 || ex.n_classes > kMaxExpand || ex.n_classes > K || K > kMaxWidth)
+  if (ex.n_classes < 1 || ex.n_classes > kMaxExpand || ex.n_classes > K || K > kMaxWidth ||
+      (dtype == 0 && !wscale))
     return hipErrorInvalidValue;
   if (dtype == 0)
-    fwd_tile<false, false>(M, N, [&](auto t) {
-      fwd_expand_launch<false, typename decltype(t)::type>(X, W, bias, ex, M, N, K, H, gpart, s);
+    fwd_tile_split<false>(M, N, [&](auto t) {
+      using S = typename decltype(t)::type;
+      const dim3 grid(S::tiles(M, N));
+      const float *x = static_cast<const float *>(X), *w = static_cast<const float *>(W);
+      if (H)
+        hipLaunchKernelGGL((k_fwd_expand_split<S, true>), grid, dim3(S::threads), 0, s, x, w, bias,
+                           ex, wscale, M, N, K, H, gpart);
+      else
+        hipLaunchKernelGGL((k_fwd_expand_split<S, false>), grid, dim3(S::threads), 0, s, x, w,
+                           bias, ex, wscale, M, N, K, H, gpart);
     });
   else
     fwd_tile<true, false>(M, N, [&](auto t) {
-      fwd_expand_launch<true, typename decltype(t)::type>(X, W, bias, ex, M, N, K, H, gpart, s);
+      using T = typename decltype(t)::type;
+      const dim3 grid(T::tiles(M, N));
+      const uint16_t *x = static_cast<const uint16_t *>(X), *w = static_cast<const uint16_t *>(W);
+      static_assert(T::bk == nt_bk<true>(), "forward k-tile is 128 bytes");
+      if (H)
+        hipLaunchKernelGGL((k_fwd_expand<T::bm, T::bn, T::wm, T::wn, T::pf, true>), grid,
+                           dim3(T::threads), 0, s, x, w, bias, ex, M, N, K, H, gpart);
+      else
+        hipLaunchKernelGGL((k_fwd_expand<T::bm, T::bn, T::wm, T::wn, T::pf, false>), grid,
+                           dim3(T::threads), 0, s, x, w, bias, ex, M, N, K, H, gpart);
     });
   return hipGetLastError();
 }
 
 hipError_t launch_loss(const float *gpart, int ntiles, int R, int n_pos, float theta, float *g,
-                       float *c, float *lpart, float *s_out, float norm_eps, const float *s_in,
-                       float *cs, hipStream_t s) {
-  if (cs && !s_in) return hipErrorInvalidValue;
+                       float *c, float *lpart, float *s_out, float norm_eps,
+                       const float *s_in, float *cs, const float *xscale, float *q,
+                       int32_t *mpart, hipStream_t s) {
+  if ((cs && !s_in) || (q == nullptr) != (mpart == nullptr)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_loss_rows, dim3(loss_blocks(R)), dim3(kLossRows), 0, s, gpart, ntiles, R,
-                     n_pos, theta, g, c, lpart, s_out, norm_eps, s_in, cs);
+                     n_pos, theta, g, c, lpart, s_out, norm_eps, s_in, cs, xscale, q, mpart);
   return hipGetLastError();
 }
 
@@ -2522,45 +3601,65 @@ hipError_t launch_adam_dense(const float *G, int M, int N, float *W, float *mW, 
   return hipGetLastError();
 }
 
-template <bool BF16, class T>
-void dw_launch(const float *H, const float *c, const void *Xh, const float *cs, int M, int N,
-               int K, float *W, float *mW, float *vW, uint16_t *Wb, float *b, float *mb,
-               float *vb, const AdamArgs &a, const LossFinish &lf, hipStream_t s) {
-  const dim3 grid(T::tiles(M, N)), block(T::threads);
-  if constexpr (BF16)
-    hipLaunchKernelGGL((k_dw_adam_bf16<T::bm, T::bn, T::bk, T::wm, T::wn, T::pf>), grid, block,
-                       0, s, H, c, static_cast<const uint16_t *>(Xh), M, N, K, W, mW, vW, Wb, b,
-                       mb, vb, a, lf);
-  else if (cs)
-    hipLaunchKernelGGL((k_dw_adam_f32<T::bm, T::bn, T::bk, T::wm, T::wn, T::pf, true>), grid,
-                       block, 0, s, H, c, static_cast<const float *>(Xh), cs, M, N, K, W, mW,
-                       vW, Wb, b, mb, vb, a, lf);
-  else
-    hipLaunchKernelGGL((k_dw_adam_f32<T::bm, T::bn, T::bk, T::wm, T::wn, T::pf, false>), grid,
-                       block, 0, s, H, c, static_cast<const float *>(Xh), cs, M, N, K, W, mW,
-                       vW, Wb, b, mb, vb, a, lf);
+template <class T>
+void dw_launch_bf16(const float *H, const float *c, const uint16_t *Xh, int M, int N, int K,
+                    float *W, float *mW, float *vW, uint16_t *Wb, float *b, float *mb, float *vb,
+                    const AdamArgs &a, const LossFinish &lf, hipStream_t s) {
+  hipLaunchKernelGGL((k_dw_adam_bf16<T::bm, T::bn, T::bk, T::wm, T::wn, T::pf>),
+                     dim3(T::tiles(M, N)), dim3(T::threads), 0, s, H, c, Xh, M, N, K, W, mW, vW,
+                     Wb, b, mb, vb, a, lf);
 }
 
-hipError_t launch_dw_adam(int dtype, const float *H, const float *c, const void *Xh,
-                          const float *cs, int M, int N, int K, float *W, float *mW,
-                          float *vW, uint16_t *Wb, float *b, float *mb, float *vb,
-                          const AdamArgs &a, const LossFinish &lf, hipStream_t s) {
-  const bool big = dw_big(M, N, dtype);
-  if (dtype == 0) {
-    if (big)
-      dw_launch<false, DwBig>(H, c, Xh, cs, M, N, K, W, mW, vW, Wb, b, mb, vb, a, lf, s);
-    else
-      dw_launch<false, DwSmall>(H, c, Xh, cs, M, N, K, W, mW, vW, Wb, b, mb, vb, a, lf, s);
-  } else {
-    if (cs) return hipErrorInvalidValue;  // bf16 operands arrive normalised
-    if (big && DwBigBf16::tiles(M, N) >= 2 * kCUs)
-      dw_launch<true, DwBigBf16>(H, c, Xh, nullptr, M, N, K, W, mW, vW, Wb, b, mb, vb, a, lf, s);
-    else if (big)
-      dw_launch<true, DwFullBf16>(H, c, Xh, nullptr, M, N, K, W, mW, vW, Wb, b, mb, vb, a, lf, s);
-    else
-      dw_launch<true, DwSmallBf16>(H, c, Xh, nullptr, M, N, K, W, mW, vW, Wb, b, mb, vb, a, lf,
-                                   s);
-  }
+hipError_t launch_dw_adam_bf16(const float *H, const float *c, const uint16_t *Xh, int M, int N,
+                               int K, float *W, float *mW, float *vW, uint16_t *Wb, float *b,
+                               float *mb, float *vb, const AdamArgs &a, const LossFinish &lf,
+                               hipStream_t s) {
+  if (DwBigBf16::tiles(M, N) >= 2 * kCUs)
+    dw_launch_bf16<DwBigBf16>(H, c, Xh, M, N, K, W, mW, vW, Wb, b, mb, vb, a, lf, s);
+  else if (DwBigBf16::tiles(M, N) >= kCUs)
+    dw_launch_bf16<DwFullBf16>(H, c, Xh, M, N, K, W, mW, vW, Wb, b, mb, vb, a, lf, s);
+  else
+    dw_launch_bf16<DwSmallBf16>(H, c, Xh, M, N, K, W, mW, vW, Wb, b, mb, vb, a, lf, s);
+  return hipGetLastError();
+}
+
+template <class T>
+void dw_launch_f32(const float *H, const float *c, const float *Xh, const float *cs, int M, int N,
+                   int K, float *W, float *mW, float *vW, float *b, float *mb, float *vb,
+                   const AdamArgs &a, const LossFinish &lf, hipStream_t s) {
+  const dim3 grid(T::tiles(M, N)), block(T::threads);
+  if (cs)
+    hipLaunchKernelGGL((k_dw_adam_f32<T::bm, T::bn, T::bk, T::wm, T::wn, T::pf, true>), grid,
+                       block, 0, s, H, c, Xh, cs, M, N, K, W, mW, vW, b, mb, vb, a, lf);
+  else
+    hipLaunchKernelGGL((k_dw_adam_f32<T::bm, T::bn, T::bk, T::wm, T::wn, T::pf, false>), grid,
+                       block, 0, s, H, c, Xh, cs, M, N, K, W, mW, vW, b, mb, vb, a, lf);
+}
+
+hipError_t launch_dw_adam_f32(const float *H, const float *c, const float *Xh, const float *cs,
+                              int M, int N, int K, float *W, float *mW, float *vW, float *b,
+                              float *mb, float *vb, const AdamArgs &a, const LossFinish &lf,
+                              hipStream_t s) {
+  // The large tile also takes grids of at least three quarters of the CUs:
+  // layer 0's 2000x784 weights (224 tiles) ran 91 us on it over 2048 rows,
+  // 98 us on 416 small tiles.
+  if (4 * DwBig::tiles(M, N) >= 3 * kCUs)
+    dw_launch_f32<DwBig>(H, c, Xh, cs, M, N, K, W, mW, vW, b, mb, vb, a, lf, s);
+  else
+    dw_launch_f32<DwSmall>(H, c, Xh, cs, M, N, K, W, mW, vW, b, mb, vb, a, lf, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_dw_adam_split(const float *H, const float *Xh, const DwRows &rows, int M, int N,
+                              int K, float *W, float *mW, float *vW, float *b, float *mb,
+                              float *vb, const AdamArgs &a, const LossFinish &lf, hipStream_t s) {
+  if (M > kMaxWidth || N > kMaxWidth || M % 4 || N % 4 || K < 1 || rows.nm < 1)
+    return hipErrorInvalidValue;
+  dw_tile_split(M, N, [&](auto t) {
+    using S = typename decltype(t)::type;
+    hipLaunchKernelGGL(k_dw_adam_split<S>, dim3(S::tiles(M, N)), dim3(S::threads), 0, s, H, Xh,
+                       rows, M, N, K, W, mW, vW, b, mb, vb, a, lf);
+  });
   return hipGetLastError();
 }
 
@@ -2616,6 +3715,20 @@ hipError_t launch_po_dz(const float *H, const float *G, const float *Wc, int R, 
   head_classes(C, [&](auto cc) {
     hipLaunchKernelGGL(k_po_dz<decltype(cc)::value>, dim3(cdiv((long)R * (D / 4), kBlock)),
                        dim3(kBlock), 0, s, H, G, Wc, R, D, C, dZ, ones);
+  });
+  return hipGetLastError();
+}
+
+int po_row_blocks(int rows) { return (int)cdiv(rows, kBlock / 64); }
+
+hipError_t launch_po_dz_rows(const float *H, const float *G, const float *Wc, int R, int D, int C,
+                             float *dZ, float *ones, const float *xscale, float *q,
+                             int32_t *mpart, hipStream_t s) {
+  if (R <= 0) return hipSuccess;
+  if (C < 1 || C > kHeadMaxClasses || D % 4) return hipErrorInvalidValue;
+  head_classes(C, [&](auto cc) {
+    hipLaunchKernelGGL(k_po_dz_rows<decltype(cc)::value>, dim3(po_row_blocks(R)), dim3(kBlock), 0,
+                       s, H, G, Wc, R, D, C, dZ, ones, xscale, q, mpart);
   });
   return hipGetLastError();
 }
