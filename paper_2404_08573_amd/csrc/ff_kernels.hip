@@ -2095,12 +2095,17 @@ __device__ __forceinline__ void tn_split_loop(const float *__restrict__ Hm,
       }
     }
     if constexpr (DB) {
+      // eight rows to themselves first: a chain of K / (16 WK) sums in place of
+      // K / (2 WK), relative error 1.2e-7 for 2.0e-7 at 2048 rows, WK = 2
+      float2 d8 = make_float2(0.f, 0.f);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const float c = ct[t + j];
-        db.x += c * ar[j][0];
-        db.y += c * ar[j][1];
+        d8.x += c * ar[j][0];
+        d8.y += c * ar[j][1];
       }
+      db.x += d8.x;
+      db.y += d8.y;
     }
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
