@@ -2954,30 +2954,40 @@ __global__ __launch_bounds__(kBlock) void k_head_logits(HeadFeatures hf, int n, 
   }
 }
 
-// dZ of four consecutive units j.. of row r: sum over classes of G[r][c] Wc[c][j],
-// through the ReLU's derivative (h = 0 wherever z <= 0).
-template <int CC>
-__device__ __forceinline__ float4 po_dz4(const float *__restrict__ H, const float *__restrict__ G,
-                                         const float *__restrict__ Wc, int r, int j, int D,
-                                         int C) {
-  const float4 h = ld4(H + (size_t)r * D + j);
-  float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+// dZ of four consecutive units j.. of rows r0..r0+RB-1: sum over classes of
+// G[r][c] Wc[c][j], through the ReLU's derivative (h = 0 wherever z <= 0).  Rows
+// past R are row R-1 again.  The classifier's columns are loaded once for all rows.
+template <int CC, int RB>
+__device__ __forceinline__ void po_dz4(const float *__restrict__ H, const float *__restrict__ G,
+                                       const float *__restrict__ Wc, int r0, int j, int R, int D,
+                                       int C, float4 *g) {
+  float4 h[RB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    h[i] = ld4(H + (size_t)min(r0 + i, R - 1) * D + j);
+    g[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
 #pragma unroll
   for (int c = 0; c < CC; ++c) {
     const int cc = min(c, C - 1);
-    const float gl = G[(size_t)r * C + cc];
     const float4 w = ld4(Wc + (size_t)cc * D + j);
-    const float gc = c < C ? gl : 0.f;
-    g.x += gc * w.x;
-    g.y += gc * w.y;
-    g.z += gc * w.z;
-    g.w += gc * w.w;
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      const float gl = G[(size_t)min(r0 + i, R - 1) * C + cc];
+      const float gc = c < C ? gl : 0.f;
+      g[i].x += gc * w.x;
+      g[i].y += gc * w.y;
+      g[i].z += gc * w.z;
+      g[i].w += gc * w.w;
+    }
   }
-  g.x = h.x > 0.f ? g.x : 0.f;
-  g.y = h.y > 0.f ? g.y : 0.f;
-  g.z = h.z > 0.f ? g.z : 0.f;
-  g.w = h.w > 0.f ? g.w : 0.f;
-  return g;
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    g[i].x = h[i].x > 0.f ? g[i].x : 0.f;
+    g[i].y = h[i].y > 0.f ? g[i].y : 0.f;
+    g[i].z = h[i].z > 0.f ? g[i].z : 0.f;
+    g[i].w = h[i].w > 0.f ? g[i].w : 0.f;
+  }
 }
 
 // Backprop of a layer's classifier into the layer: one thread per 4
@@ -2992,13 +3002,19 @@ __global__ __launch_bounds__(kBlock) void k_po_dz(const float *__restrict__ H,
   const int d4 = D >> 2;
   if (q >= R * d4) return;
   const int r = q / d4, j = 4 * (q % d4);
-  st4(dZ + (size_t)r * D + j, po_dz4<CC>(H, G, Wc, r, j, D, C));
+  float4 g;
+  po_dz4<CC, 1>(H, G, Wc, r, j, R, D, C, &g);
+  st4(dZ + (size_t)r * D + j, g);
   if (j == 0) ones[r] = 1.f;
 }
 
-// The same with one wave per row, which then also has the row's largest |dZ|:
-// the row factors of the fp32 weight gradient (q, and the largest exponent of
-// the workgroup's four rows in mpart).
+// The same with a workgroup per kPoRows rows, which then also has each row's
+// largest |dZ|: the row factors of the fp32 weight gradient (q, and the largest
+// exponent of the rows in mpart).  The time is the latency of a thread's
+// dependent rounds of loads: with the workgroup's threads side by side on a
+// row, 2000 units are two rounds (1024 x 2000 with 10 classes: 7.6 us, where a
+// wave per row, in eight rounds, took 16.2).
+constexpr int kPoRows = 4;
 template <int CC>
 __global__ __launch_bounds__(kBlock) void k_po_dz_rows(const float *__restrict__ H,
                                                        const float *__restrict__ G,
@@ -3008,33 +3024,46 @@ __global__ __launch_bounds__(kBlock) void k_po_dz_rows(const float *__restrict__
                                                        const float *__restrict__ xscale,
                                                        float *__restrict__ q,
                                                        int32_t *__restrict__ mpart) {
-  __shared__ int em[kBlock / 64];
+  constexpr int NWV = kBlock / 64;
+  static_assert(kPoRows <= 64, "one lane per row");
+  __shared__ uint32_t wm[NWV][kPoRows];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r = blockIdx.x * (kBlock / 64) + wave;
-  if (lane == 0) em[wave] = -1000;
-  if (r < R) {  // uniform per wave
-    uint32_t m = 0;
-    for (int j = 4 * lane; j < D; j += 256) {
-      const float4 g = po_dz4<CC>(H, G, Wc, r, j, D, C);
-      st4(dZ + (size_t)r * D + j, g);
-      m = max(max(m, max(abs_bits(g.x), abs_bits(g.y))), max(abs_bits(g.z), abs_bits(g.w)));
-    }
+  const int r0 = blockIdx.x * kPoRows;
+  uint32_t m[kPoRows];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
-    if (lane == 0) {
-      const RowFactor f = row_factor(__uint_as_float(m), input_exp(xscale, r));
-      ones[r] = 1.f;
-      q[r] = f.q;
-      em[wave] = f.m;
+  for (int i = 0; i < kPoRows; ++i) m[i] = 0;
+  for (int j = 4 * threadIdx.x; j < D; j += 4 * kBlock) {
+    float4 g[kPoRows];
+    po_dz4<CC, kPoRows>(H, G, Wc, r0, j, R, D, C, g);
+#pragma unroll
+    for (int i = 0; i < kPoRows; ++i) {
+      if (r0 + i < R) st4(dZ + (size_t)(r0 + i) * D + j, g[i]);
+      m[i] = max(max(m[i], max(abs_bits(g[i].x), abs_bits(g[i].y))),
+                 max(abs_bits(g[i].z), abs_bits(g[i].w)));
     }
+  }
+#pragma unroll
+  for (int i = 0; i < kPoRows; ++i) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m[i] = max(m[i], (uint32_t)__shfl_xor((int)m[i], o));
+    if (lane == 0) wm[wave][i] = m[i];
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int e = em[0];
+  if (wave != 0) return;
+  int e = -1000;
+  if (lane < kPoRows && r0 + lane < R) {
+    const int r = r0 + lane;
+    uint32_t mr = wm[0][lane];
 #pragma unroll
-    for (int w = 1; w < kBlock / 64; ++w) e = max(e, em[w]);
-    mpart[blockIdx.x] = e;
+    for (int w = 1; w < NWV; ++w) mr = max(mr, wm[w][lane]);
+    const RowFactor f = row_factor(__uint_as_float(mr), input_exp(xscale, r));
+    ones[r] = 1.f;
+    q[r] = f.q;
+    e = f.m;
   }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) e = max(e, __shfl_xor(e, o));
+  if (lane == 0) mpart[blockIdx.x] = e;
 }
 
 // Classifier weight-gradient partials.  A workgroup covers 64 consecutive
@@ -3724,7 +3753,7 @@ hipError_t launch_po_dz(const float *H, const float *G, const float *Wc, int R, 
   return hipGetLastError();
 }
 
-int po_row_blocks(int rows) { return (int)cdiv(rows, kBlock / 64); }
+int po_row_blocks(int rows) { return (int)cdiv(rows, kPoRows); }
 
 hipError_t launch_po_dz_rows(const float *H, const float *G, const float *Wc, int R, int D, int C,
                              float *dZ, float *ones, const float *xscale, float *q,
