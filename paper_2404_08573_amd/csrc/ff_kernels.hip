@@ -3129,8 +3129,13 @@ __global__ __launch_bounds__(kBlock) void k_head_grad(HeadFeatures hf,
   }
 }
 
-// Adam on the head.  Block 0 also reduces db and the loss over the rows: each
-// thread sums a fixed strided subset, then a fixed-order tree in LDS.
+// Adam on the head.  Workgroup 0 reduces db and the loss over the rows: each
+// thread sums a fixed strided subset, then a fixed-order tree; the others
+// update 4 weights per thread.  Both are chains of loads: with db in a
+// workgroup of its own, four rows and eight splits of loads in flight, 1024
+// rows of 10 classes and 2000 features take 5.7 us (10.7 with one row and one
+// split at a time and db after workgroup 0's weights).
+template <int CC>  // class-count bound, as in k_head_logits
 __global__ __launch_bounds__(kBlock) void k_head_adam(const float *__restrict__ part, int splits,
                                                       const float *__restrict__ G,
                                                       const float *__restrict__ lrow, int n,
@@ -3141,18 +3146,27 @@ __global__ __launch_bounds__(kBlock) void k_head_adam(const float *__restrict__ 
                                                       float *__restrict__ mbv,
                                                       float *__restrict__ vbv, AdamArgs ad,
                                                       float *__restrict__ loss) {
-  const size_t i = 4 * ((size_t)blockIdx.x * kBlock + threadIdx.x);
-  const size_t total = (size_t)C * D;
-  if (i < total) {
-    float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int sp = 0; sp < splits; ++sp) {
-      const float4 v = ld4(part + (size_t)sp * total + i);
-      g.x += v.x;
-      g.y += v.y;
-      g.z += v.z;
-      g.w += v.w;
-    }
+  if (blockIdx.x != 0) {
+    const size_t i = 4 * ((size_t)(blockIdx.x - 1) * kBlock + threadIdx.x);
+    const size_t total = (size_t)C * D;
+    if (i >= total) return;
     float4 p = ld4(W + i), m = ld4(mW + i), v = ld4(vW + i);
+    float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto add = [&](const float4 &t) {
+      g.x += t.x;
+      g.y += t.y;
+      g.z += t.z;
+      g.w += t.w;
+    };
+    int sp = 0;
+    for (; sp + 8 <= splits; sp += 8) {
+      float4 t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t[u] = ld4(part + (size_t)(sp + u) * total + i);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) add(t[u]);
+    }
+    for (; sp < splits; ++sp) add(ld4(part + (size_t)sp * total + i));
     adam_update(p.x, m.x, v.x, g.x, ad);
     adam_update(p.y, m.y, v.y, g.y, ad);
     adam_update(p.z, m.z, v.z, g.z, ad);
@@ -3160,36 +3174,59 @@ __global__ __launch_bounds__(kBlock) void k_head_adam(const float *__restrict__ 
     st4(W + i, p);
     st4(mW + i, m);
     st4(vW + i, v);
+    return;
   }
-  if (blockIdx.x != 0) return;
-  __shared__ float red[kHeadMaxClasses + 1][kBlock];
-  float acc[kHeadMaxClasses + 1];
+  constexpr int RU = 4;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  float acc[CC + 1];  // the classes (those past C: never used), the loss
 #pragma unroll
-  for (int c = 0; c <= kHeadMaxClasses; ++c) acc[c] = 0.f;
-  for (int r = threadIdx.x; r < n; r += kBlock) {
+  for (int c = 0; c <= CC; ++c) acc[c] = 0.f;
+  auto rows = [&](int r, auto U) {  // rows r, r + kBlock, ..
+    constexpr int u_n = decltype(U)::value;
+    float t[u_n][CC + 1];
 #pragma unroll
-    for (int c = 0; c < kHeadMaxClasses; ++c)
-      if (c < C) acc[c] += G[(size_t)r * C + c];
-    if (lrow) acc[kHeadMaxClasses] += lrow[r];
-  }
+    for (int u = 0; u < u_n; ++u) {
 #pragma unroll
-  for (int c = 0; c <= kHeadMaxClasses; ++c) red[c][threadIdx.x] = acc[c];
-  __syncthreads();
-  for (int st = kBlock / 2; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st)
+      for (int c = 0; c < CC; ++c) t[u][c] = G[(size_t)(r + u * kBlock) * C + min(c, C - 1)];
+      t[u][CC] = lrow ? lrow[r + u * kBlock] : 0.f;
+    }
 #pragma unroll
-      for (int c = 0; c <= kHeadMaxClasses; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + st];
+    for (int u = 0; u < u_n; ++u)
+#pragma unroll
+      for (int c = 0; c <= CC; ++c) acc[c] += t[u][c];
+  };
+  int r = tid;
+  for (; r + (RU - 1) * kBlock < n; r += RU * kBlock) rows(r, std::integral_constant<int, RU>{});
+  for (; r < n; r += kBlock) rows(r, std::integral_constant<int, 1>{});
+  // threads 128 apart, then 64, then within wave 0
+  static_assert(kBlock == 256, "tree below");
+  __shared__ float red[2][CC + 1][64];
+  for (int h = 2; h > 0; h >>= 1) {
+    if (wave >= h && wave < 2 * h)
+#pragma unroll
+      for (int c = 0; c <= CC; ++c) red[wave - h][c][lane] = acc[c];
+    __syncthreads();
+    if (wave < h)
+#pragma unroll
+      for (int c = 0; c <= CC; ++c) acc[c] += red[wave][c][lane];
     __syncthreads();
   }
-  if ((int)threadIdx.x < C) {
-    const int c = threadIdx.x;
-    float p = bvec[c], m = mbv[c], v = vbv[c];
-    adam_update(p, m, v, red[c][0], ad);
-    bvec[c] = p;
-    mbv[c] = m;
-    vbv[c] = v;
+  if (wave != 0) return;
+  float db = 0.f;
+#pragma unroll
+  for (int c = 0; c < CC; ++c) {
+    const float v = wave_sum(acc[c]);
+    if (lane == c) db = v;
   }
-  if (threadIdx.x == 0 && loss) loss[0] = red[kHeadMaxClasses][0] / (float)n;
+  const float ls = wave_sum(acc[CC]);
+  if (lane < C) {
+    float p = bvec[lane], m = mbv[lane], v = vbv[lane];
+    adam_update(p, m, v, db, ad);
+    bvec[lane] = p;
+    mbv[lane] = m;
+    vbv[lane] = v;
+  }
+  if (lane == 0 && loss) loss[0] = ls / (float)n;
 }
 
 // ---------------------------------------------------------------------------
@@ -3787,9 +3824,11 @@ hipError_t launch_head_adam(const float *part, int splits, const float *G, const
                             float *mb, float *vb, const AdamArgs &a, float *loss,
                             hipStream_t s) {
   if (C < 1 || C > kHeadMaxClasses || D % 4) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_head_adam, dim3(std::max(1u, cdiv((long)C * D / 4, kBlock))),
-                     dim3(kBlock), 0, s, part, splits, G, lrow, n, C, D, W, mW, vW, b, mb, vb,
-                     a, loss);
+  head_classes(C, [&](auto cc) {
+    hipLaunchKernelGGL(k_head_adam<decltype(cc)::value>,
+                       dim3(1 + cdiv((long)C * D / 4, kBlock)), dim3(kBlock), 0, s, part, splits,
+                       G, lrow, n, C, D, W, mW, vW, b, mb, vb, a, loss);
+  });
   return hipGetLastError();
 }
 
