@@ -2790,6 +2790,37 @@ __device__ __forceinline__ int head_block(const HeadFeatures &hf, int f, int &j)
   return blk;
 }
 
+// Softmax of row r's logits z (class c's on lane c; the whole wave is active): its
+// logits, argmax, gradient G = (p - onehot) / n and loss, each unless null.
+__device__ __forceinline__ void head_softmax(float z, int r, int n, int C, int lane,
+                                             const int32_t *__restrict__ labels,
+                                             float *__restrict__ logits,
+                                             int32_t *__restrict__ pred, float *__restrict__ G,
+                                             float *__restrict__ lrow) {
+  float zmax = -INFINITY;
+  int arg = 0;
+  for (int c = 0; c < C; ++c) {
+    const float v = __shfl(z, c);
+    if (v > zmax) {
+      zmax = v;
+      arg = c;
+    }
+  }
+  const float e = lane < C ? expf(z - zmax) : 0.f;
+  const float esum = wave_sum(e);
+  // labels outside [0, C) are clamped into it (unspecified result, no stray access)
+  const int y = labels ? min(max(labels[r], 0), C - 1) : 0;
+  const float zy = __shfl(z, y);  // the true class's logit, from its lane
+  if (lane < C) {
+    if (logits) logits[(size_t)r * C + lane] = z;
+    if (G) G[(size_t)r * C + lane] = (e / esum - (lane == y ? 1.f : 0.f)) / (float)n;
+  }
+  if (lane == 0) {
+    if (pred) pred[r] = arg;
+    if (lrow) lrow[r] = logf(esum) - (zy - zmax);  // -log p_y
+  }
+}
+
 // One wave per kHeadRows rows: the C dot products of each row over its
 // feature blocks, reduced across the wave, then the softmax on lanes 0..C-1.
 // Lanes run over features, 4 each, so a chunk is 256 consecutive features of
@@ -2925,33 +2956,131 @@ __global__ __launch_bounds__(kBlock) void k_head_logits(HeadFeatures hf, int n, 
   for (int q = 0; q < RW; ++q) {
     const int r = r0 + q;
     if (r >= n) break;  // uniform per wave
-    float z = 0.f, zmax = -INFINITY;
-    int arg = 0;
+    float z = 0.f;
 #pragma unroll
     for (int c = 0; c < CC; ++c)
       if (c < C) {
         float v = wave_sum(acc[q][c]);
         for (int k = 0; k < hf.n_bias; ++k) v += hf.bias[k][c];
         if (lane == c) z = v;
-        if (v > zmax) {
-          zmax = v;
-          arg = c;
-        }
       }
-    const float e = lane < C ? expf(z - zmax) : 0.f;
-    const float esum = wave_sum(e);
-    // labels outside [0, C) are clamped into it (unspecified result, no stray access)
-    const int y = labels ? min(max(labels[r], 0), C - 1) : 0;
-    const float zy = __shfl(z, y);  // the true class's logit, from its lane (whole wave active)
-    if (lane < C) {
-      if (logits) logits[(size_t)r * C + lane] = z;
-      if (G) G[(size_t)r * C + lane] = (e / esum - (lane == y ? 1.f : 0.f)) / (float)n;
+    head_softmax(z, r, n, C, lane, labels, logits, pred, G, lrow);
+  }
+}
+
+// The same for batches too small to fill the chip with the kernel above, whose
+// waves walk all of a row's chunks: a workgroup per kHeadSplitRows rows, the
+// chunks dealt over its waves, which read the weights from L2 straight into
+// registers, the next chunk's loads in flight beside each chunk.  The waves'
+// sums meet in LDS and are added in wave order.
+constexpr int kHeadSplitRows = 4, kHeadSplitWaves = 8;
+template <int CC>  // class-count bound, as in k_head_logits
+__global__ __launch_bounds__(kHeadSplitWaves * 64) void k_head_logits_split(
+    HeadFeatures hf, int n, int C, const int32_t *__restrict__ labels, float *__restrict__ logits,
+    int32_t *__restrict__ pred, float *__restrict__ G, float *__restrict__ lrow) {
+  constexpr int RW = kHeadSplitRows, NW = kHeadSplitWaves;
+  static_assert(RW == 4, "the reduction hands a row to each quarter wave");
+  __shared__ float part[NW][RW][CC];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r0 = blockIdx.x * RW;
+  int ng = 0;
+  for (int b = 0; b < hf.n_blocks; ++b) ng += (hf.d[b] / 4 + 63) / 64;
+  float acc[RW][CC];
+#pragma unroll
+  for (int q = 0; q < RW; ++q)
+#pragma unroll
+    for (int c = 0; c < CC; ++c) acc[q][c] = 0.f;
+
+  struct Chunk {
+    float4 x[RW], w[CC];
+    float s[RW];
+    bool in;
+  };
+  // the wave's chunks: wave, wave + NW, ...; (lb, lc): the block of the next
+  // one and its chunk in it
+  int lb = 0, lc = wave;
+  auto load = [&](Chunk &k) {
+    int nc = (hf.d[lb] / 4 + 63) / 64;
+    while (lc >= nc) {  // ends: load runs only for chunks below ng
+      lc -= nc;
+      nc = (hf.d[++lb] / 4 + 63) / 64;
     }
-    if (lane == 0) {
-      if (pred) pred[r] = arg;
-      if (lrow) lrow[r] = logf(esum) - (zy - zmax);  // -log p_y
+    const int d = hf.d[lb], d4 = d >> 2, j = lc * 64 + lane;
+    const size_t o = 4 * (size_t)min(j, d4 - 1);
+    k.in = j < d4;
+#pragma unroll
+    for (int q = 0; q < RW; ++q) {
+      const int r = min(r0 + q, n - 1);
+      k.x[q] = ld4(hf.h[lb] + (size_t)r * d + o);
+      k.s[q] = hf.s[lb] ? hf.s[lb][r] : 1.f;
+    }
+#pragma unroll
+    for (int c = 0; c < CC; ++c)
+      k.w[c] = ld4(hf.w[lb] + (size_t)min(c, C - 1) * hf.ldw[lb] + o);
+    lc += NW;
+  };
+  auto compute = [&](Chunk &k) {
+    if (!k.in) return;
+#pragma unroll
+    for (int q = 0; q < RW; ++q) {
+      float4 x = k.x[q];
+      x.x *= k.s[q];
+      x.y *= k.s[q];
+      x.z *= k.s[q];
+      x.w *= k.s[q];
+#pragma unroll
+      for (int c = 0; c < CC; ++c)
+        acc[q][c] += x.x * k.w[c].x + x.y * k.w[c].y + x.z * k.w[c].z + x.w * k.w[c].w;
+    }
+  };
+  const int cnt = (ng - wave + NW - 1) / NW;  // 0 for waves past the last chunk
+  if (cnt > 0) {
+    Chunk a, b;
+    load(a);
+    int i = 0;
+    for (; i + 2 < cnt; i += 2) {
+      load(b);
+      compute(a);
+      load(a);
+      compute(b);
+    }
+    if (i + 1 < cnt) {
+      load(b);
+      compute(a);
+      compute(b);
+    } else {
+      compute(a);
     }
   }
+
+  // Half the rows to each half wave, one to each quarter, then a sum over its 16 lanes.
+  float sum[CC];
+#pragma unroll
+  for (int c = 0; c < CC; ++c) {
+    const bool hi = lane & 32, odd = lane & 16;
+    const float t0 = (hi ? acc[2][c] : acc[0][c]) + __shfl_xor(hi ? acc[0][c] : acc[2][c], 32);
+    const float t1 = (hi ? acc[3][c] : acc[1][c]) + __shfl_xor(hi ? acc[1][c] : acc[3][c], 32);
+    sum[c] = (odd ? t1 : t0) + __shfl_xor(odd ? t0 : t1, 16);
+  }
+#pragma unroll
+  for (int m = 8; m; m >>= 1)
+#pragma unroll
+    for (int c = 0; c < CC; ++c) sum[c] += __shfl_xor(sum[c], m);
+  if ((lane & 15) == 0) {
+#pragma unroll
+    for (int c = 0; c < CC; ++c) part[wave][lane >> 4][c] = sum[c];
+  }
+  __syncthreads();
+  const int r = r0 + wave;
+  if (wave >= RW || r >= n) return;  // a wave per row from here on
+  float z = 0.f;
+  if (lane < C) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w) z += part[w][wave][lane];
+    for (int k = 0; k < hf.n_bias; ++k) z += hf.bias[k][lane];
+  }
+  head_softmax(z, r, n, C, lane, labels, logits, pred, G, lrow);
 }
 
 // dZ of four consecutive units j.. of rows r0..r0+RB-1: sum over classes of
@@ -3772,9 +3901,19 @@ hipError_t launch_head_logits(const HeadFeatures &f, int n, int C, const int32_t
     if (f.d[b] <= 0 || f.d[b] % 4 || f.ldw[b] < f.d[b] ||
         ((long)(C - 1) * f.ldw[b] + f.d[b]) * 4 >= (1l << 31))
       return hipErrorInvalidValue;
+  // Up to eight rows per CU the row-walking kernel leaves it one workgroup or
+  // none.  Change from it to the split one, 10 classes x 2000 / 6000 features:
+  // 16 rows -10 / -18 us, 1024 rows -11 / -20 us (of 16 / 28 us), 2048 rows
+  // -6 / -11 us; 4096 rows 0 / 0, 10000 rows +10 / +5 us (twice the weight reads).
+  const bool split = n <= 8 * kCUs;
   head_classes(C, [&](auto cc) {
-    hipLaunchKernelGGL(k_head_logits<decltype(cc)::value>, dim3(cdiv(n, kBlock / 64 * kHeadRows)),
-                       dim3(kBlock), 0, s, f, n, C, labels, logits, pred, G, lrow);
+    if (split)
+      hipLaunchKernelGGL(k_head_logits_split<decltype(cc)::value>, dim3(cdiv(n, kHeadSplitRows)),
+                         dim3(64 * kHeadSplitWaves), 0, s, f, n, C, labels, logits, pred, G, lrow);
+    else
+      hipLaunchKernelGGL(k_head_logits<decltype(cc)::value>,
+                         dim3(cdiv(n, kBlock / 64 * kHeadRows)), dim3(kBlock), 0, s, f, n, C,
+                         labels, logits, pred, G, lrow);
   });
   return hipGetLastError();
 }
