@@ -1138,6 +1138,10 @@ __global__ __launch_bounds__(S::threads, 2) void k_fwd_split(
 }
 
 // fp32 shared-base layer-0 forward (see k_fwd_expand) from the split product.
+// Classes that a workgroup of the label-expanding forward writes: those of its
+// blockIdx.y, of gridDim.y groups.
+__device__ __forceinline__ int expand_classes(int C) { return (C + gridDim.y - 1) / gridDim.y; }
+
 template <class S, bool STORE_H>
 __global__ __launch_bounds__(S::threads, 2) void k_fwd_expand_split(
     const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ bias,
@@ -1154,15 +1158,16 @@ __global__ __launch_bounds__(S::threads, 2) void k_fwd_expand_split(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wk = wave % S::WK, wm = wave / S::WK / S::WN, wn = wave / S::WK % S::WN;
   const int li = lane & 31, kg = lane >> 5;
-  const int C = ex.n_classes;
+  const int C = ex.n_classes, cn = expand_classes(C), c0 = blockIdx.y * cn;
+  const int c1 = min(c0 + cn, C);
   floatx16 own[S::OWN];
   float bv[S::OWN];
   nt_split_product<S>(X, W, bias, nullptr, nullptr, wscale, M, N, K, m0, n0, st, own, bv);
 
   float *gs = sm0;  // [C][CB][BM] goodness partials
   float *wl = sm1;  // [BN][kMaxExpand] label columns of W
-  for (int i = tid; i < S::BN * C; i += S::threads) {
-    const int j = i / C, c = i % C;
+  for (int i = tid; i < S::BN * (c1 - c0); i += S::threads) {
+    const int j = i / (c1 - c0), c = c0 + i % (c1 - c0);
     wl[j * kMaxExpand + c] = W[(size_t)min(n0 + j, N - 1) * K + c];
   }
   __syncthreads();
@@ -1174,7 +1179,7 @@ __global__ __launch_bounds__(S::threads, 2) void k_fwd_expand_split(
     float sr[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) sr[r] = ex.scale[min(m0 + rl + acc_row(r, kg), M - 1)];
-    for (int c = 0; c < C; ++c) {
+    for (int c = c0; c < c1; ++c) {
       const float wc = wl[cl * kMaxExpand + c];
       float hsq[16];
 #pragma unroll
@@ -1191,8 +1196,8 @@ __global__ __launch_bounds__(S::threads, 2) void k_fwd_expand_split(
   }
   __syncthreads();
   const size_t MO = (size_t)M * C;
-  for (int i = tid; i < S::BM * C; i += S::threads) {
-    const int t = i % S::BM, c = i / S::BM;
+  for (int i = tid; i < S::BM * (c1 - c0); i += S::threads) {
+    const int t = i % S::BM, c = c0 + i / S::BM;
     const int row = m0 + t;
     if (row < M) {
       float g = 0.f;
@@ -1653,7 +1658,8 @@ __global__ __launch_bounds__(WM *WN * 64) void k_fwd_expand(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
   const int li = lane & 31, kg = lane >> 5;
-  const int C = ex.n_classes;
+  const int C = ex.n_classes, cn = expand_classes(C), c0 = blockIdx.y * cn;
+  const int c1 = min(c0 + cn, C);
 
   floatx16 acc[MB][NB];
   nt_mainloop<true, BM, BN, WM, WN, NBUF>(X, W, M, N, K, m0, n0,
@@ -1663,8 +1669,8 @@ __global__ __launch_bounds__(WM *WN * 64) void k_fwd_expand(
   // the tile's label columns of W.
   float *gs = smf;
   float *wl = smf + kMaxExpand * WN * BM;
-  for (int i = tid; i < BN * C; i += NT) {
-    const int j = i / C, c = i % C;
+  for (int i = tid; i < BN * (c1 - c0); i += NT) {
+    const int j = i / (c1 - c0), c = c0 + i % (c1 - c0);
     const int col = min(n0 + j, N - 1);
     wl[j * kMaxExpand + c] = bf16_bits_to_f(W[(size_t)col * K + c]);
   }
@@ -1676,7 +1682,7 @@ __global__ __launch_bounds__(WM *WN * 64) void k_fwd_expand(
   for (int q = 0; q < MB * 16; ++q)
     sr[q] = ex.scale[min(rbase + (q >> 4) * 32 + acc_row(q & 15, kg), M - 1)];
 
-  for (int c = 0; c < C; ++c) {
+  for (int c = c0; c < c1; ++c) {
     float hsq[MB * 16];
 #pragma unroll
     for (int q = 0; q < MB * 16; ++q) hsq[q] = 0.f;
@@ -1713,8 +1719,8 @@ __global__ __launch_bounds__(WM *WN * 64) void k_fwd_expand(
   }
   __syncthreads();
   const size_t MO = (size_t)M * C;
-  for (int i = tid; i < BM * C; i += NT) {
-    const int t = i % BM, c = i / BM;
+  for (int i = tid; i < BM * (c1 - c0); i += NT) {
+    const int t = i % BM, c = c0 + i / BM;
     const int row = m0 + t;
     if (row < M) {
       float g = 0.f;
@@ -3689,6 +3695,17 @@ hipError_t launch_fwd_f32(const float *X, const float *W, const float *bias, con
   return hipGetLastError();
 }
 
+// Class groups of the label-expanding forward.  A grid that leaves CUs idle deals
+// each tile's classes, up to C groups of them, to CUs of their own: every group
+// computes the tile's product again, which takes less time than the classes' serial
+// epilogue (37 inputs, 784 -> 2000, 10 classes, bf16: 32 tiles 17.7 us, in five
+// groups of two classes 11.8 us).
+unsigned expand_groups(long tiles, int C) {
+  const int g = (int)std::min<long>(C, std::max<long>(1, kCUs / tiles));
+  const int per = (C + g - 1) / g;
+  return (unsigned)((C + per - 1) / per);
+}
+
 hipError_t launch_fwd_expand(int dtype, const void *X, const void *W, const float *bias,
                              const LabelExpand &ex, const float *wscale, int M, int N, int K,
                              float *H, float *gpart, hipStream_t s) {
@@ -3699,7 +3716,7 @@ hipError_t launch_fwd_expand(int dtype, const void *X, const void *W, const floa
   if (dtype == 0)
     fwd_tile_split<false>(M, N, [&](auto t) {
       using S = typename decltype(t)::type;
-      const dim3 grid(S::tiles(M, N));
+      const dim3 grid(S::tiles(M, N), expand_groups(S::tiles(M, N), ex.n_classes));
       const float *x = static_cast<const float *>(X), *w = static_cast<const float *>(W);
       if (H)
         hipLaunchKernelGGL((k_fwd_expand_split<S, true>), grid, dim3(S::threads), 0, s, x, w, bias,
@@ -3711,7 +3728,7 @@ hipError_t launch_fwd_expand(int dtype, const void *X, const void *W, const floa
   else
     fwd_tile<true, false>(M, N, [&](auto t) {
       using T = typename decltype(t)::type;
-      const dim3 grid(T::tiles(M, N));
+      const dim3 grid(T::tiles(M, N), expand_groups(T::tiles(M, N), ex.n_classes));
       const uint16_t *x = static_cast<const uint16_t *>(X), *w = static_cast<const uint16_t *>(W);
       static_assert(T::bk == nt_bk<true>(), "forward k-tile is 128 bytes");
       if (H)
